@@ -427,7 +427,7 @@ struct sp_ctx {
     // scratch of the plan stream and of the ingest stream
     uint32_t *tmp_k = nullptr, *tmp_v = nullptr, *hist = nullptr;
     ScanWs ws_plan;
-    uint32_t *itmp_k = nullptr, *itmp_v = nullptr, *ihist = nullptr;
+    SortWs ws_sort{};
     ScanWs ws_ingest;
     int32_t *sel_state = nullptr, *sel_hist = nullptr;
     uint32_t *vk0 = nullptr, *vv0 = nullptr, *vk1 = nullptr;
@@ -965,14 +965,13 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         TRY(dalloc(h, &b.ids, N));
         TRY(dalloc(h, &b.bag_off, TB1));
         TRY(dalloc(h, &b.bag_of, N));
-        TRY(dalloc(h, &b.skeys, N));
         TRY(dalloc(h, &b.perm, N));
         TRY(dalloc(h, &b.sbag, N));
         TRY(dalloc(h, &b.ukeys, N));
         TRY(dalloc(h, &b.eslot, N));
         TRY(dalloc(h, &b.inv, N));
         TRY(dalloc(h, &b.seg_off, N + 1));
-        TRY(dalloc(h, &b.seg_chunk0, N));
+        TRY(dalloc(h, &b.seg_chunk0, N + 1));
         TRY(dalloc(h, &b.chunk_desc, nchunk_max));
         TRY(dalloc(h, &b.multi, multi_capacity(N, h->chunk)));
         TRY(dalloc(h, &b.scal, T + 3));
@@ -1003,8 +1002,6 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     }
     TRY(dalloc(h, &h->tmp_k, N));
     TRY(dalloc(h, &h->tmp_v, N));
-    TRY(dalloc(h, &h->itmp_k, N));
-    TRY(dalloc(h, &h->itmp_v, N));
     TRY(dalloc(h, &h->vk0, NM));
     TRY(dalloc(h, &h->vv0, NM));
     TRY(dalloc(h, &h->vk1, NM));
@@ -1014,7 +1011,16 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         TRY(dalloc(h, &h->pf_own_uidx, N));
         TRY(dalloc(h, &h->pf_flag, (int64_t)h->pf_depth * N));
     }
-    TRY(dalloc(h, &h->ihist, radix_hist_entries(N)));
+    {
+        const SortWsSize z = sort_ws_size(N);
+        TRY(dalloc(h, &h->ws_sort.e[0], z.entries));
+        h->ws_sort.e[1] = h->ws_sort.e[0] + z.entries / 2;
+        TRY(dalloc(h, &h->ws_sort.hist, z.hist));
+        TRY(dalloc(h, &h->ws_sort.tcount, z.tiles));
+        TRY(dalloc(h, &h->ws_sort.tpre, z.tiles));
+        TRY(dalloc(h, &h->ws_sort.arrived, 2));
+        h->ws_sort.err = h->ws_sort.arrived + 1;
+    }
     TRY(dalloc(h, &h->cnt, 1));
     TRY(dalloc(h, &h->cnt_part, (int64_t)PART_COPIES * PART_WORDS + 1));
     {
@@ -1116,6 +1122,8 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     HIPCHK(nullptr, hipMemsetAsync(h->sel_hist, 0, sizeof(int32_t) * MAX_TABLES * SEL_BINS, h->s_plan));
     HIPCHK(nullptr, hipMemsetAsync(h->sel_state, 0, sizeof(int32_t) * 3 * MAX_TABLES, h->s_plan));
     HIPCHK(nullptr, hipMemsetAsync(h->cnt, 0, sizeof(DevCounters), h->s_plan));
+    HIPCHK(nullptr, hipMemsetAsync(h->ws_sort.arrived, 0, sizeof(int32_t) * 2, h->s_plan));
+    HIPCHK(nullptr, hipMemsetAsync(h->ws_sort.tcount, 0, sizeof(uint64_t) * sort_ws_size(N).tiles, h->s_plan));
     HIPCHK(nullptr, hipMemsetAsync(h->cnt_part, 0, sizeof(int32_t) * (PART_COPIES * PART_WORDS + 1), h->s_plan));
     for (ScanWs *ws : {&h->ws_plan, &h->ws_ingest}) {
         HIPCHK(nullptr, hipMemsetAsync(ws->status, 0, sizeof(uint64_t) * LB_WORDS * ws->max_tiles, h->s_plan));
@@ -1321,8 +1329,8 @@ static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead,
     } else if (caller_waits) {
         h->wait_cons_event = true;  // recorded by launch_ingest once the inputs are read
     }
-    launch_ingest(h->tb, b, ids, off, bt.batch, bt.nnz, h->key_bits, h->chunk, h->max_table_ids,
-                  h->max_ids, h->nchunk_max, h->itmp_k, h->itmp_v, h->ihist, h->ws_ingest,
+    launch_ingest(h->tb, b, ids, off, bt.batch, bt.nnz, h->chunk, h->max_table_ids, h->max_ids,
+                  h->nchunk_max, h->ws_sort, h->ws_ingest,
                   caller_waits ? h->ev_consumed : nullptr, ic, si);
     CHECK_LAUNCH(h);
     if (h->ws_ingest.overflow) return fail(h, SP_ERR_HIP, "internal: scan workspace too small");

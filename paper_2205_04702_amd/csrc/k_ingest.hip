@@ -25,57 +25,588 @@ void launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s)
 
 void launch_zero_i32(int32_t *p, int64_t n, hipStream_t s) { launch_fill_i32(p, n, 0, s); }
 
-// ---------------------------------------------------------------- keys and bags
+// ---------------------------------------------------------------- bags
 
-// One launch over max(nnz, nbags) threads, two independent jobs:
-//  * position j < nnz: key = table << row_bits | row, where the table is the
-//    one whose span [bag_off[t*B], bag_off[(t+1)*B]) contains j; rows out of
-//    range raise ERR_ID_RANGE and are clamped so nothing downstream leaves
-//    its array;
-//  * bag g < nbags: validate the offsets (non-decreasing, from 0 to nnz;
-//    ERR_OFFSETS otherwise, ranges clamped into [0, nnz)), write bag_of[j] = g
-//    for the bag's positions and copy the offsets into the window ring (when
-//    they are read from the caller's device memory); the first bag of each
-//    table also checks the table's ID count against max_table_ids (when set,
-//    ERR_TABLE_IDS).
-__global__ void __launch_bounds__(BLOCK) k_prepare(Tables tb, const int32_t *ids,
-                                                   const int32_t *bag_off, int32_t *bag_off_copy,
-                                                   int32_t B, int64_t nnz, int64_t nbags,
-                                                   int64_t max_table_ids, uint32_t *keys,
-                                                   uint32_t *pos, int32_t *bag_of, int32_t *err)
+// Bag bookkeeping of a batch.  One wave takes 64 consecutive bags, lane i
+// their i-th: it validates the offsets (non-decreasing, from 0 to nnz;
+// ERR_OFFSETS otherwise, ranges clamped into [0, nnz)), copies them into the
+// window ring (when they are read from the caller's device memory) and checks
+// each table's ID count against max_table_ids (when set, ERR_TABLE_IDS); then
+// the wave walks the positions its bags cover, 64 at a time, and writes
+// bag_of for them, each lane finding its position's bag among the 64 offsets
+// by a search over the lanes.  Stores are whole 256-byte lines; one thread per
+// bag writing its positions one by one took 0.24 ms alone (0.9 ms beside the
+// training kernels) for 21M IDs.
+__device__ __forceinline__ void mark_bags(int64_t first, const int32_t *bag_off,
+                                          int32_t *bag_off_copy, int32_t B, int64_t nnz,
+                                          int64_t nbags, int64_t max_table_ids, int32_t *bag_of,
+                                          int32_t *err)
 {
-    const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (i < nnz) {
-        int lo = 0, hi = tb.T - 1;  // largest t with bag_off[t*B] <= i
-        while (lo < hi) {
-            int mid = (lo + hi + 1) >> 1;
-            if ((int64_t)bag_off[(int64_t)mid * B] <= i) lo = mid; else hi = mid - 1;
-        }
-        int32_t row = ids[i];
-        if (row < 0 || (int64_t)row >= tb.rows[lo]) {
-            atomicOr(err, ERR_ID_RANGE);
-            row = 0;
-        }
-        keys[i] = ((uint32_t)lo << tb.row_bits) | (uint32_t)row;
-        pos[i] = (uint32_t)i;
-    }
-    if (i < nbags) {
-        int64_t lo = bag_off[i], hi = bag_off[i + 1];
+    const int lane = lane_id();
+    const int64_t g = first + lane;
+    const bool in = g < nbags;
+    const int64_t gc = in ? g : nbags - 1;
+    int64_t lo = bag_off[gc], hi = bag_off[gc + 1];
+    int32_t bad = 0;
+    if (in) {
         if (bag_off_copy != bag_off) {
-            bag_off_copy[i] = (int32_t)lo;
-            if (i == nbags - 1) bag_off_copy[i + 1] = (int32_t)hi;
+            bag_off_copy[g] = (int32_t)lo;
+            if (g == nbags - 1) bag_off_copy[g + 1] = (int32_t)hi;
         }
-        bool bad = lo > hi || lo < 0 || hi > nnz || (i == 0 && lo != 0) ||
-                   (i == nbags - 1 && hi != nnz);
-        if (bad) {
-            atomicOr(err, ERR_OFFSETS);
-            lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
-            hi = hi < lo ? lo : (hi > nnz ? nnz : hi);
+        if (lo > hi || lo < 0 || hi > nnz || (g == 0 && lo != 0) || (g == nbags - 1 && hi != nnz))
+            bad |= ERR_OFFSETS;
+        if (max_table_ids > 0 && g % B == 0 && (int64_t)bag_off[g + B] - lo > max_table_ids)
+            bad |= ERR_TABLE_IDS;
+    }
+    if (bad) atomicOr(err, bad);
+    lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
+    hi = hi < 0 ? 0 : (hi > nnz ? nnz : hi);
+    if (!in) lo = hi;  // lanes past the last bag start where it ends
+    const int32_t lo32 = (int32_t)lo;
+    const int64_t p0 = __shfl(lo32, 0, WAVE), p1 = __shfl((int32_t)hi, WAVE - 1, WAVE);
+    for (int64_t base = p0; base < p1; base += WAVE) {
+        const int32_t p = (int32_t)(base + lane);
+        int k = 0;  // the last of the 64 bags that starts at or before p
+#pragma unroll
+        for (int o = WAVE / 2; o > 0; o >>= 1) {
+            const int32_t x = __shfl(lo32, k + o, WAVE);
+            if (x <= p) k += o;
         }
-        for (int64_t j = lo; j < hi; ++j) bag_of[j] = (int32_t)i;
-        if (max_table_ids > 0 && i % B == 0 &&
-            (int64_t)bag_off[i + B] - bag_off[i] > max_table_ids)
-            atomicOr(err, ERR_TABLE_IDS);
+        const int64_t bag = first + k < nbags ? first + k : nbags - 1;
+        if (p < p1) bag_of[p] = (int32_t)bag;
+    }
+}
+
+__global__ void __launch_bounds__(BLOCK) k_bags(const int32_t *bag_off, int32_t *bag_off_copy,
+                                                int32_t B, int64_t nnz, int64_t nbags,
+                                                int64_t max_table_ids, int32_t *bag_of,
+                                                int32_t *err)
+{
+    const int64_t first = ((int64_t)blockIdx.x * (BLOCK / WAVE) + wave_id()) * WAVE;
+    if (first < nbags)
+        mark_bags(first, bag_off, bag_off_copy, B, nnz, nbags, max_table_ids, bag_of, err);
+}
+
+// ---------------------------------------------------------------- general path: segmented sort
+//
+// A batch arrives table by table, so its keys (table << row_bits | row) only
+// have to be put in order within each table: a stable LSD radix sort of every
+// table's IDs by the bits its row count needs, all tables in the same
+// launches.  Table t takes ceil(bits / SORT_BITS) passes of equal digits; the
+// tables that need fewer passes join at a later launch, so all of them end in
+// the same buffer.  A table's first pass reads the caller's IDs themselves
+// (validated: rows out of range raise ERR_ID_RANGE and become row 0), later
+// ones 64-bit entries key << 32 | position.  A pass is two launches over tiles
+// of each table's span:
+//  * k_sort_hist: digit counts of every tile and of every group of G tiles
+//    (one block per group);
+//  * k_sort_scatter: one block per tile.  It adds up its digit's group counts
+//    and the tile counts of its own group (no scan in between: G is near the
+//    square root of a table's tiles, so a thread adds some 2 * G counts), ranks its
+//    entries with wave ballots, puts them in digit order in LDS and writes
+//    each digit's entries as one run.
+// What bounds it: HBM traffic, 8 bytes read and written per entry and pass
+// plus 8 for the counts: alone a pass takes 0.11 + 0.10 ms for 21M IDs and
+// 0.042 + 0.042 ms for 4.3M.  Before (11-bit digits of the whole key, entries
+// scattered one by one to 2048 bins, a scan launch per pass) 21M IDs took 3
+// passes of 0.43 ms, 4.3M IDs 2 of 0.38 ms.
+constexpr int SORT_BITS = 9;
+constexpr int SORT_BINS = 1 << SORT_BITS;
+
+// Spans, tiles and groups of the tables of a batch, from its offsets, by one
+// wave (lane t: table t) into LDS.  Offsets that go back or leave [0, nnz] (an
+// error raised by mark_bags) give disjoint spans inside it all the same.
+struct SortLay {
+    int32_t beg[MAX_TABLES + 1], tile0[MAX_TABLES + 1], group0[MAX_TABLES + 1];
+};
+static_assert(MAX_TABLES == WAVE, "one table per lane");
+__device__ __forceinline__ void sort_layout(SortLay &l, const int32_t *bag_off, int32_t T,
+                                            int32_t B, int64_t nnz, int tile_len, int G)
+{
+    const int lane = lane_id();
+    int64_t end = lane < T ? bag_off[(int64_t)(lane + 1) * B] : 0;
+    end = end < 0 ? 0 : (end > nnz ? nnz : end);
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int32_t x = __shfl_up((int32_t)end, o, WAVE);
+        if (lane >= o && x > end) end = x;
+    }
+    int32_t prev = __shfl_up((int32_t)end, 1, WAVE);
+    if (lane == 0) prev = 0;
+    const int32_t tiles = (int32_t)((end - prev + tile_len - 1) / tile_len);
+    const int32_t ti = wave_incl_scan(tiles), gi = wave_incl_scan((tiles + G - 1) / G);
+    l.beg[lane + 1] = (int32_t)end;
+    l.tile0[lane + 1] = ti;
+    l.group0[lane + 1] = gi;
+    if (lane == 0) l.beg[0] = l.tile0[0] = l.group0[0] = 0;
+}
+// The table whose tiles (or groups) hold index i: the number of tables that end at or
+// before it.  first: the array's first of MAX_TABLES + 1 entries.
+__device__ __forceinline__ int sort_table(const int32_t *first, int64_t i)
+{
+    return __popcll(__ballot((int64_t)first[lane_id() + 1] <= i));
+}
+
+// The digit of table t in launch q of `passes`: false when the table starts
+// later.  first: this launch is the table's first.
+__device__ __forceinline__ bool sort_digit(int64_t rows, int q, int passes, int &shift, int &dbits,
+                                           bool &first)
+{
+    const int bits = rows > 2 ? 64 - __clzll((unsigned long long)(rows - 1)) : 1;
+    const int np = (bits + SORT_BITS - 1) / SORT_BITS;
+    const int p = q - (passes - np);
+    dbits = (bits + np - 1) / np;
+    shift = p * dbits;
+    first = p == 0;
+    return p >= 0;
+}
+
+// Entry i of a table: its ID as an entry, or the entry an earlier pass left.
+__device__ __forceinline__ uint64_t sort_entry(bool first, const int32_t *ids, const uint64_t *in,
+                                               int64_t i, int t, int row_bits, int64_t rows,
+                                               bool &bad)
+{
+    if (!first) return in[i];
+    int32_t row = ids[i];
+    if (row < 0 || (int64_t)row >= rows) {
+        bad = true;
+        row = 0;
+    }
+    return (uint64_t)(((uint32_t)t << row_bits) | (uint32_t)row) << 32 | (uint64_t)(uint32_t)i;
+}
+
+// NT * ITEMS entries per tile.  Blocks past `groups` of the first launch mark
+// the bags instead.
+template <int NT, int ITEMS>
+__global__ void __launch_bounds__(NT) k_sort_hist(Tables tb, const int32_t *ids,
+                                                  const int32_t *bag_off, int32_t *bag_off_copy,
+                                                  int32_t B, int64_t nnz, int64_t nbags,
+                                                  int64_t max_table_ids, int32_t *bag_of,
+                                                  int32_t groups, const uint64_t *in, int q,
+                                                  int passes, int G, uint32_t *thist,
+                                                  uint32_t *ghist, int32_t *err)
+{
+    constexpr int TILE = NT * ITEMS;
+    constexpr int PER = (SORT_BINS + NT - 1) / NT;
+    __shared__ SortLay lay;
+    __shared__ uint32_t h[SORT_BINS];
+    __shared__ int32_t t_s;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= groups) {
+        const int64_t first =
+            ((int64_t)(blockIdx.x - groups) * (NT / WAVE) + wave_id()) * WAVE;
+        if (first < nbags)
+            mark_bags(first, bag_off, bag_off_copy, B, nnz, nbags, max_table_ids, bag_of, err);
+        return;
+    }
+    // consecutive groups (one table's) on one XCD, as in the scatter
+    const int64_t gr = xcd_block(blockIdx.x, groups);
+    if (tid < WAVE) {
+        sort_layout(lay, bag_off, tb.T, B, nnz, TILE, G);
+        const int t = sort_table(lay.group0, gr);
+        if (tid == 0) t_s = t;
+    }
+    for (int d = tid; d < SORT_BINS; d += NT) h[d] = 0;
+    __syncthreads();
+    const int t = t_s;
+    if (t >= tb.T) return;  // past the last group (uniform)
+    const int64_t rows = tb.rows[t];
+    int shift, dbits;
+    bool first, bad = false;
+    if (!sort_digit(rows, q, passes, shift, dbits, first)) return;
+    const int bins = 1 << dbits;
+    const uint32_t mask = (uint32_t)bins - 1u;
+    const int64_t end = lay.beg[t + 1];
+    const int tile_a = lay.tile0[t] + (int)(gr - lay.group0[t]) * G;
+    const int tile_b = tile_a + G < lay.tile0[t + 1] ? tile_a + G : lay.tile0[t + 1];
+    uint32_t sum[PER] = {};
+    for (int tile = tile_a; tile < tile_b; ++tile) {
+        const int64_t base = (int64_t)lay.beg[t] + (int64_t)(tile - lay.tile0[t]) * TILE;
+        uint32_t key[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const int64_t i = base + r * NT + tid;
+            key[r] = 0;
+            if (i < end)
+                key[r] = (uint32_t)(sort_entry(first, ids, in, i, t, tb.row_bits, rows, bad) >> 32);
+        }
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            if (base + r * NT + tid < end) atomicAdd(&h[(key[r] >> shift) & mask], 1u);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int d = k * NT + tid;
+            if (d < bins) {
+                const uint32_t c = h[d];
+                thist[(int64_t)tile * SORT_BINS + d] = c;
+                sum[k] += c;
+                h[d] = 0;
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = k * NT + tid;
+        if (d < bins) ghist[gr * SORT_BINS + d] = sum[k];
+    }
+    if (bad) atomicOr(err, ERR_ID_RANGE);
+}
+
+template <int NT, int ITEMS>
+__global__ void __launch_bounds__(NT) k_sort_scatter(Tables tb, const int32_t *ids,
+                                                     const int32_t *bag_off, int32_t B,
+                                                     int64_t nnz, const uint64_t *in,
+                                                     uint64_t *out, int q, int passes, int G,
+                                                     const uint32_t *thist, const uint32_t *ghist)
+{
+    constexpr int TILE = NT * ITEMS;
+    constexpr int NW = NT / WAVE;
+    constexpr int PER = (SORT_BINS + NT - 1) / NT;
+    __shared__ SortLay lay;
+    __shared__ uint64_t buf[TILE];
+    __shared__ uint32_t wc[NW][SORT_BINS];
+    __shared__ uint32_t to[SORT_BINS];  // digit's output index less its place in the tile
+    __shared__ uint64_t lds[NW];
+    __shared__ int32_t t_s;
+    const int tid = threadIdx.x, w = wave_id(), lane = lane_id();
+    // consecutive tiles (one table's) on one XCD: the runs that neighbouring
+    // tiles write to one digit share its L2
+    const int64_t tile = xcd_block(blockIdx.x, gridDim.x);
+    if (tid < WAVE) {
+        sort_layout(lay, bag_off, tb.T, B, nnz, TILE, G);
+        const int t = sort_table(lay.tile0, tile);
+        if (tid == 0) t_s = t;
+    }
+    for (int i = tid; i < NW * SORT_BINS; i += NT) (&wc[0][0])[i] = 0;
+    __syncthreads();
+    const int t = t_s;
+    if (t >= tb.T) return;  // past the last tile (uniform)
+    const int64_t rows = tb.rows[t];
+    int shift, dbits;
+    bool first, bad = false;
+    if (!sort_digit(rows, q, passes, shift, dbits, first)) return;
+    const int bins = 1 << dbits;
+    const uint32_t mask = (uint32_t)bins - 1u;
+    const int64_t beg = lay.beg[t], end = lay.beg[t + 1];
+    const int64_t base = beg + (tile - lay.tile0[t]) * TILE;
+    const int n = (int)(end - base < TILE ? end - base : TILE);
+    // wave w holds its own contiguous share of the tile, 64 entries at a time
+    uint64_t e[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = w * (ITEMS * WAVE) + r * WAVE + lane;
+        e[r] = i < n ? sort_entry(first, ids, in, base + i, t, tb.row_bits, rows, bad) : 0ull;
+    }
+    // thread tid owns digits tid * PER ..: the table's entries of each digit,
+    // and those in tiles before this one
+    uint32_t total[PER] = {}, before[PER] = {};
+    {
+        const int g0 = lay.group0[t], g1 = lay.group0[t + 1];
+        const int lt = (int)(tile - lay.tile0[t]);
+        const int mine = g0 + lt / G;
+        const int d0 = tid * PER;
+        if (d0 < bins) {
+#pragma unroll 8
+            for (int g = g0; g < g1; ++g)
+#pragma unroll
+                for (int k = 0; k < PER; ++k) {
+                    const uint32_t x = ghist[(int64_t)g * SORT_BINS + d0 + k];
+                    total[k] += x;
+                    before[k] += g < mine ? x : 0u;
+                }
+#pragma unroll 8
+            for (int64_t u = tile - lt % G; u < tile; ++u)
+#pragma unroll
+                for (int k = 0; k < PER; ++k) before[k] += thist[u * SORT_BINS + d0 + k];
+        }
+    }
+    // rank of each entry among the wave's entries with its digit
+    const uint64_t lt_mask = lanemask_lt();
+    uint32_t rk[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = w * (ITEMS * WAVE) + r * WAVE + lane;
+        const bool valid = i < n;
+        const uint32_t d = (uint32_t)(e[r] >> (32 + shift)) & mask;
+        uint64_t peers = __ballot(valid);
+        for (int b = 0; b < dbits; ++b) {
+            const uint32_t bit = (d >> b) & 1u;
+            const uint64_t bb = __ballot(bit);
+            peers &= bit ? bb : ~bb;
+        }
+        const int leader = valid ? __ffsll((unsigned long long)peers) - 1 : lane;
+        uint32_t prior = 0;
+        if (valid && leader == lane) {
+            prior = wc[w][d];
+            wc[w][d] = prior + (uint32_t)__popcll(peers);
+        }
+        prior = __shfl(prior, leader, WAVE);
+        rk[r] = prior + (uint32_t)__popcll(peers & lt_mask);
+    }
+    __syncthreads();
+    // digits: where each starts in the table and in the tile, in one scan
+    uint32_t cnt[PER], tsum = 0, csum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = tid * PER + k;
+        cnt[k] = 0;
+        if (d < bins)
+            for (int x = 0; x < NW; ++x) cnt[k] += wc[x][d];
+        else
+            total[k] = 0;
+        tsum += total[k];
+        csum += cnt[k];
+    }
+    uint64_t all;
+    uint64_t ex = block_excl_scan_n<NT, uint64_t>((uint64_t)tsum << 32 | csum, lds, all);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = tid * PER + k;
+        if (d < bins) {
+            uint32_t run = (uint32_t)ex;
+            to[d] = (uint32_t)beg + (uint32_t)(ex >> 32) + before[k] - run;
+            for (int x = 0; x < NW; ++x) {
+                const uint32_t c = wc[x][d];
+                wc[x][d] = run;
+                run += c;
+            }
+        }
+        ex += (uint64_t)total[k] << 32 | cnt[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = w * (ITEMS * WAVE) + r * WAVE + lane;
+        if (i < n) {
+            const uint32_t d = (uint32_t)(e[r] >> (32 + shift)) & mask;
+            const uint32_t p = wc[w][d] + rk[r];
+            buf[p < (uint32_t)n ? p : (uint32_t)(n - 1)] = e[r];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = r * NT + tid;
+        if (i < n) {
+            const uint64_t x = buf[i];
+            const uint32_t p = to[(uint32_t)(x >> (32 + shift)) & mask] + (uint32_t)i;
+            // never write past the batch, whatever the counts say
+            out[p < (uint64_t)nnz ? p : (uint64_t)(nnz - 1)] = x;
+        }
+    }
+}
+
+// ---------------------------------------------------------------- general path: runs
+//
+// The sorted entries fall into runs of equal keys.  k_runs<false> counts, per
+// tile of the batch, the runs and the backward chunks (BWD_CHUNK positions of
+// one run at most) that start in it and the runs longer than one chunk; its
+// last block to finish turns the counts into prefixes and writes the batch's
+// totals and error bits.  k_runs<true> finds the same starts again and writes
+// everything at its place: unique keys, run offsets, chunk descriptors, and
+// per sorted entry the bag (sbag) and the run of its position (inv).  The
+// second reading of the entries (8 bytes each) buys tiles that need no order
+// among them, so consecutive tiles stay on one XCD and the scattered stores of
+// inv, which stay within a table's span, meet in its L2: 0.10 + 0.48 ms for
+// 21M IDs, 0.03 + 0.07 ms for 4.3M.  Before, two single-pass scans did this in 0.9 + 1.2 ms for 21M IDs and 0.22 + 0.70 ms
+// for 4.3M: the stores of a line came from all XCDs, every descriptor was
+// stored by a serial loop, and every long run took an atomic on one address.
+constexpr uint32_t KEY_PAST = 0xFFFFFFFFu;  // after the last entry (keys are below 2^31)
+
+// First index of [0, i] whose run reaches i (sorted keys, i > 0), by one wave:
+// steps of 64 times the last one, then back down.
+__device__ __forceinline__ int64_t run_start(const uint64_t *e, int64_t i, uint32_t key)
+{
+    const int lane = lane_id();
+    int64_t step = 1;
+    // in all indices from `hi` to i the key is the run's
+    int64_t hi = i;
+    while (true) {
+        const int64_t p = hi - (int64_t)(lane + 1) * step;
+        const bool same = p >= 0 && (uint32_t)(e[p >= 0 ? p : 0] >> 32) == key;
+        const uint64_t bal = __ballot(same);
+        const int k = bal == ~0ull ? WAVE : __ffsll((unsigned long long)~bal) - 1;
+        hi -= (int64_t)k * step;  // the last probed index that still has the key
+        if (k == WAVE) {
+            step *= WAVE;
+        } else if (step > 1) {
+            step /= WAVE;
+        } else {
+            return hi;
+        }
+    }
+}
+
+template <int NT, int ITEMS, bool EMIT>
+__global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *bag_off, int32_t T,
+                                             int32_t B, int64_t nnz, const int32_t *bag_of,
+                                             BatchDev b, int64_t n_multi_cap, uint64_t *tcount,
+                                             int4 *tpre, int32_t tiles, int32_t *arrived,
+                                             int32_t *err)
+{
+    constexpr int TILE = NT * ITEMS;
+    constexpr int HALO = BWD_CHUNK;
+    __shared__ uint32_t key[1 + TILE + HALO];  // key[1 + i]: entry i of the tile
+    __shared__ uint32_t pos[EMIT ? TILE : 1], seg[EMIT ? TILE : 1];
+    __shared__ uint64_t lds[NT / WAVE];
+    __shared__ int32_t ldsm[NT / WAVE];
+    __shared__ int64_t start_s;
+    __shared__ int64_t total_s;
+    __shared__ int32_t last_s;
+    const int tid = threadIdx.x;
+    const int64_t tile = xcd_block(blockIdx.x, tiles);
+    const int64_t base = tile * TILE;
+    if (tid < WAVE) {  // entries there are: the largest table end (offsets may be malformed)
+        int64_t end = tid < T ? bag_off[(int64_t)(tid + 1) * B] : 0;
+        end = end < 0 ? 0 : (end > nnz ? nnz : end);
+#pragma unroll
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const int32_t x = __shfl_xor((int32_t)end, o, WAVE);
+            if (x > end) end = x;
+        }
+        if (tid == 0) total_s = end;
+    }
+    __syncthreads();
+    const int64_t total = total_s;
+    const int n = (int)(total - base < 0 ? 0 : (total - base < TILE ? total - base : TILE));
+    for (int i = tid; i < 1 + TILE + HALO; i += NT) {
+        const int64_t g = base + i - 1;
+        const uint64_t x = g >= 0 && g < total ? e[g] : (uint64_t)KEY_PAST << 32;
+        key[i] = (uint32_t)(x >> 32);
+        if (EMIT && i >= 1 && i <= TILE) pos[i - 1] = (uint32_t)x;
+    }
+    __syncthreads();
+    if (tid < WAVE) {  // where the run that reaches into the tile starts
+        int64_t s = base;
+        if (n > 0 && base > 0 && key[0] == key[1]) s = run_start(e, base, key[1]);
+        if (tid == 0) start_s = s;
+    }
+    // thread tid owns entries tid * ITEMS ..
+    uint32_t heads = 0;
+    int32_t last_head = -1;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = tid * ITEMS + k;
+        if (i < n && (base + i == 0 || key[i] != key[1 + i])) {
+            heads |= 1u << k;
+            last_head = i;
+        }
+    }
+    // the last head before this thread's entries
+    int32_t incl = last_head;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const int32_t x = __shfl_up(incl, o, WAVE);
+        if (lane_id() >= o && x > incl) incl = x;
+    }
+    if (lane_id() == WAVE - 1) ldsm[wave_id()] = incl;
+    __syncthreads();
+    int32_t prev = __shfl_up(incl, 1, WAVE);
+    if (lane_id() == 0) prev = -1;
+    for (int x = 0; x < wave_id(); ++x) prev = ldsm[x] > prev ? ldsm[x] : prev;
+    int64_t run0 = prev >= 0 ? base + prev : start_s;
+    uint32_t starts = 0, longs = 0;  // chunk starts; heads of runs longer than a chunk
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = tid * ITEMS + k;
+        if (i >= n) continue;
+        const bool head = (heads >> k) & 1u;
+        if (head) run0 = base + i;
+        if ((base + i - run0) % BWD_CHUNK == 0) starts |= 1u << k;
+        if (head && key[1 + i + BWD_CHUNK] == key[1 + i]) longs |= 1u << k;
+    }
+    // three counts below 2^13 in one word
+    static_assert(TILE <= 4096, "counts of a tile take 20 bits each");
+    const uint64_t mine = (uint64_t)__popc(heads) | (uint64_t)__popc(starts) << 20 |
+                          (uint64_t)__popc(longs) << 40;
+    uint64_t all;
+    const uint64_t ex = block_excl_scan_n<NT, uint64_t>(mine, lds, all);
+    constexpr uint64_t M20 = (1ull << 20) - 1;
+    if (!EMIT) {
+        if (tid == 0) {
+            // the old value is tested before the arrival below, so the word is
+            // in memory by then (cleared words never read all ones)
+            const uint64_t old = atomicExch((unsigned long long *)&tcount[tile], all);
+            last_s = atomicAdd(arrived, old == ~0ull ? 2 : 1) == tiles - 1;
+        }
+        __syncthreads();
+        if (!last_s) return;  // uniform per block
+        // ---- the last block: exclusive prefixes of the tiles, batch totals
+        const int per = (tiles + NT - 1) / NT;
+        const int a = tid * per, z = a + per < tiles ? a + per : tiles;
+        uint32_t u = 0, c = 0, m = 0;
+#pragma unroll 4
+        for (int x = a; x < z; ++x) {
+            const uint64_t v = __hip_atomic_load(&tcount[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            u += (uint32_t)(v & M20);
+            c += (uint32_t)(v >> 20 & M20);
+            m += (uint32_t)(v >> 40);
+        }
+        uint64_t tot_uc, tot_m;
+        const uint64_t uc = block_excl_scan_n<NT, uint64_t>((uint64_t)c << 32 | u, lds, tot_uc);
+        uint32_t m0 = (uint32_t)block_excl_scan_n<NT, uint64_t>((uint64_t)m, lds, tot_m);
+        uint32_t u0 = (uint32_t)uc, c0 = (uint32_t)(uc >> 32);
+#pragma unroll 4
+        for (int x = a; x < z; ++x) {
+            const uint64_t v = __hip_atomic_load(&tcount[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            tpre[x] = make_int4((int)u0, (int)c0, (int)m0, 0);
+            u0 += (uint32_t)(v & M20);
+            c0 += (uint32_t)(v >> 20 & M20);
+            m0 += (uint32_t)(v >> 40);
+        }
+        if (tid == 0) {
+            const int32_t U = (int32_t)(uint32_t)tot_uc, C = (int32_t)(tot_uc >> 32);
+            b.scal[0] = U;
+            b.scal[1] = C;
+            b.scal[2] = atomicExch(err, 0);
+            b.scal[3] = (int32_t)tot_m;
+            b.seg_off[U] = (int32_t)total;
+            b.seg_chunk0[U] = C;
+            __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+    }
+    if (n == 0) return;  // uniform per block
+    const int4 pre = tpre[tile];
+    int32_t u = pre.x + (int32_t)(ex & M20);   // runs that started before this thread's entries
+    int32_t c = pre.y + (int32_t)(ex >> 20 & M20);
+    int32_t m = pre.z + (int32_t)(ex >> 40);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = tid * ITEMS + k;
+        if (i >= n) continue;
+        const bool head = (heads >> k) & 1u, lng = (longs >> k) & 1u;
+        const uint32_t kk = key[1 + i];
+        if (head) {
+            b.ukeys[u] = kk;
+            b.seg_off[u] = (int32_t)(base + i);
+            b.seg_chunk0[u] = c;
+            if (lng && m < n_multi_cap) b.multi[m] = u;
+            m += lng;
+            ++u;
+        }
+        seg[i] = (uint32_t)(u - 1);
+        if ((starts >> k) & 1u) {
+            int len = 1;  // of the chunk: the keys are sorted, so equal ends mean equal all through
+#pragma unroll
+            for (int o = BWD_CHUNK / 2; o > 0; o >>= 1)
+                if (key[1 + i + len + o - 1] == kk) len += o;
+            const int32_t p0 = (int32_t)(base + i);
+            b.chunk_desc[c++] = make_int4(p0, p0 + len, u - 1, head && !lng ? 1 : 2);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = k * NT + tid;
+        if (i >= n) continue;
+        const uint32_t p = pos[i];
+        if (p >= (uint64_t)nnz) continue;
+        b.perm[base + i] = p;
+        b.sbag[base + i] = bag_of[p];
+        b.inv[p] = (int32_t)seg[i];
     }
 }
 
@@ -331,73 +862,6 @@ void launch_radix_sort(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, i
     }
     *in_k1 = (ki == k1);
 }
-
-// ---------------------------------------------------------------- unique keys
-
-struct HeadFlag {
-    const uint32_t *k;
-    __device__ uint32_t operator()(int64_t i, int) const
-    {
-        const uint32_t a = k[i], b = k[i > 0 ? i - 1 : i];  // both loads, no branch
-        return i == 0 || a != b;
-    }
-};
-
-// Segment (run of equal keys) bookkeeping for sorted position i.
-struct UniqueOut {
-    const uint32_t *skeys, *perm;
-    const int32_t *bag_of;
-    uint32_t *ukeys;
-    int32_t *inv, *seg_off, *sbag, *scal;
-    int64_t n;
-    __device__ void operator()(int64_t i, uint32_t e, uint32_t f, int) const
-    {
-        uint32_t seg = e + f - 1;
-        uint32_t p = perm[i];
-        if (f) {
-            ukeys[seg] = skeys[i];
-            seg_off[seg] = (int32_t)i;
-        }
-        inv[p] = (int32_t)seg;
-        sbag[i] = bag_of[p];
-        if (i == n - 1) {
-            scal[0] = (int32_t)(seg + 1);
-            seg_off[seg + 1] = (int32_t)n;
-        }
-    }
-};
-
-// Backward work split: a run of len positions becomes ceil(len / chunk) chunks.
-struct ChunkCount {
-    const int32_t *seg_off;
-    int32_t chunk;
-    __device__ uint32_t operator()(int64_t s, int) const
-    {
-        int32_t len = seg_off[s + 1] - seg_off[s];
-        return (uint32_t)((len + chunk - 1) / chunk);
-    }
-};
-// Chunk c of run s gets the descriptor {first position, end position, s,
-// chunks of s}; runs with more than one chunk are also listed in `multi`.
-struct ChunkOut {
-    const int32_t *seg_off;
-    int32_t chunk;
-    int32_t *seg_chunk0;
-    int4 *chunk_desc;
-    int32_t *multi, *scal;
-    __device__ void operator()(int64_t s, uint32_t e, uint32_t v, int) const
-    {
-        seg_chunk0[s] = (int32_t)e;
-        const int32_t s0 = seg_off[s], s1 = seg_off[s + 1];
-        for (uint32_t c = 0; c < v; ++c) {
-            const int32_t p0 = s0 + (int32_t)c * chunk;
-            chunk_desc[e + c] = make_int4(p0, p0 + chunk < s1 ? p0 + chunk : s1, (int32_t)s,
-                                          (int32_t)v);
-        }
-        if (v > 1) multi[atomicAdd(scal + 3, 1)] = (int32_t)s;  // list order is irrelevant
-        if (s == scal[0] - 1) scal[1] = (int32_t)(e + v);
-    }
-};
 
 // ---------------------------------------------------------------- tables in LDS, split by rows
 //
@@ -693,7 +1157,10 @@ __global__ void __launch_bounds__(IG_THREADS) k_ingest_table(Tables tb, const in
     }
     if (id == (uint32_t)(tb.T * S - 1) && tid == 0) {  // the batch totals
         const uint32_t U = U0 + nU;
-        if ((int64_t)U < cap_u + 1) b.seg_off[U] = (int32_t)nnz;
+        if ((int64_t)U < cap_u + 1) {
+            b.seg_off[U] = (int32_t)nnz;
+            b.seg_chunk0[U] = (int32_t)(C0 + nC);
+        }
         b.scal[0] = (int32_t)U;
         b.scal[1] = (int32_t)(C0 + nC);
         b.scal[2] = (int32_t)(before_s[3] | (uint32_t)err_s);
@@ -701,15 +1168,72 @@ __global__ void __launch_bounds__(IG_THREADS) k_ingest_table(Tables tb, const in
     }
 }
 
+// ---------------------------------------------------------------- general path: launches
+
+constexpr int64_t SORT_LARGE = 512 << 10;  // IDs from which the tiles are the long ones
+constexpr int SORT_TILE_MIN = 1024;
+
+SortWsSize sort_ws_size(int64_t n)
+{
+    // tiles (and at most as many groups, and one) of all tables: each table's
+    // last one may be short
+    const int64_t tiles = (n + SORT_TILE_MIN - 1) / SORT_TILE_MIN + MAX_TABLES + 1;
+    return {2 * n, 2 * tiles * SORT_BINS, tiles};
+}
+
+template <int NT, int ITEMS>
+static void launch_general(const Tables &tb, const BatchDev &b, const int32_t *ids,
+                           const int32_t *bag_off, int32_t B, int64_t nnz, int64_t max_table_ids,
+                           int64_t cap_u, const SortWs &sw, hipEvent_t consumed, hipStream_t s)
+{
+    constexpr int TILE = NT * ITEMS;
+    const int64_t nbags = (int64_t)tb.T * B;
+    int passes = 1;
+    for (int t = 0; t < tb.T; ++t) {
+        int bits = 1;
+        while (bits < 25 && (int64_t)1 << bits < tb.rows[t]) ++bits;
+        const int np = (bits + SORT_BITS - 1) / SORT_BITS;
+        passes = passes > np ? passes : np;
+    }
+    const int64_t flat = (nnz + TILE - 1) / TILE;
+    const int64_t tiles = flat + tb.T;  // at least those of all tables, whatever their spans
+    int G = 1;  // near the square root of a table's tiles
+    while (G < 32 && (int64_t)G * G * tb.T < flat) G *= 2;
+    const int64_t groups = flat / G + tb.T + 1;
+    uint32_t *const thist = sw.hist, *const ghist = sw.hist + tiles * SORT_BINS;
+    const int64_t bag_blocks = (nbags + NT - 1) / NT;
+    for (int q = 0; q < passes; ++q) {
+        const uint64_t *const in = sw.e[(passes - q) & 1];  // the last pass writes e[0]
+        uint64_t *const out = sw.e[(passes - 1 - q) & 1];
+        hipLaunchKernelGGL((k_sort_hist<NT, ITEMS>),
+                           dim3((unsigned)(groups + (q == 0 ? bag_blocks : 0))), dim3(NT), 0, s, tb,
+                           ids, bag_off, b.bag_off, B, nnz, nbags, max_table_ids, b.bag_of,
+                           (int32_t)groups, in, q, passes, G, thist, ghist, sw.err);
+        hipLaunchKernelGGL((k_sort_scatter<NT, ITEMS>), dim3((unsigned)tiles), dim3(NT), 0, s, tb,
+                           ids, bag_off, B, nnz, in, out, q, passes, G, (const uint32_t *)thist,
+                           (const uint32_t *)ghist);
+    }
+    // the later launches need the offsets only, from the ring's copy
+    if (consumed) (void)hipEventRecord(consumed, s);
+    const int64_t cap_m = multi_capacity(cap_u, BWD_CHUNK);
+    hipLaunchKernelGGL((k_runs<NT, ITEMS, false>), dim3((unsigned)flat), dim3(NT), 0, s,
+                       (const uint64_t *)sw.e[0], (const int32_t *)b.bag_off, tb.T, B, nnz,
+                       (const int32_t *)b.bag_of, b, cap_m, sw.tcount, sw.tpre, (int32_t)flat,
+                       sw.arrived, sw.err);
+    hipLaunchKernelGGL((k_runs<NT, ITEMS, true>), dim3((unsigned)flat), dim3(NT), 0, s,
+                       (const uint64_t *)sw.e[0], (const int32_t *)b.bag_off, tb.T, B, nnz,
+                       (const int32_t *)b.bag_of, b, cap_m, sw.tcount, sw.tpre, (int32_t)flat,
+                       sw.arrived, sw.err);
+}
+
 // Sort, deduplicate and split into backward chunks one batch of the window.
 // ids / bag_off may be the caller's device arrays (read once, here) or the
 // ring's own copies; the ring always ends up with the offsets.  Input errors
 // are recorded in the batch's own scal[2].
 void launch_ingest(const Tables &tb, const BatchDev &b, const int32_t *ids, const int32_t *bag_off,
-                   int32_t B, int64_t nnz, int key_bits, int chunk, int64_t max_table_ids,
-                   int64_t cap_u, int64_t cap_c, uint32_t *tmp_k, uint32_t *tmp_v,
-                   uint32_t *hist, ScanWs &ws, hipEvent_t consumed, const IngestCons &ic,
-                   hipStream_t s)
+                   int32_t B, int64_t nnz, int chunk, int64_t max_table_ids,
+                   int64_t cap_u, int64_t cap_c, const SortWs &sw, ScanWs &ws,
+                   hipEvent_t consumed, const IngestCons &ic, hipStream_t s)
 {
     const int64_t nbags = (int64_t)tb.T * B;
     if (nnz > 0 && ingest_in_lds(max_table_ids, B)) {
@@ -730,30 +1254,23 @@ void launch_ingest(const Tables &tb, const BatchDev &b, const int32_t *ids, cons
                            S, ic.counter, ic.target, ic.word, ic.seq);
         return;
     }
-    launch_zero_i32(b.scal, 4, s);
-    // place the keys so that the final sort pass lands in skeys/perm
-    const int passes = radix_passes(nnz, key_bits);
-    uint32_t *k0 = (passes & 1) ? tmp_k : b.skeys, *v0 = (passes & 1) ? tmp_v : b.perm;
-    uint32_t *k1 = (passes & 1) ? b.skeys : tmp_k, *v1 = (passes & 1) ? b.perm : tmp_v;
-    const int64_t nthr = nnz > nbags ? nnz : nbags;
-    if (nthr > 0)
-        hipLaunchKernelGGL(k_prepare, dim3((unsigned)((nthr + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0,
-                           s, tb, ids, bag_off, b.bag_off, B, nnz, nbags, max_table_ids, k0, v0,
-                           b.bag_of, b.scal + 2);
-    else if (bag_off != b.bag_off)
-        (void)hipMemcpyAsync(b.bag_off, bag_off, sizeof(int32_t), hipMemcpyDeviceToDevice, s);
-    if (consumed) (void)hipEventRecord(consumed, s);  // the inputs are not read after this point
-    if (nnz > 0) {
-        bool in_k1 = false;
-        launch_radix_sort(k0, v0, k1, v1, nnz, key_bits, hist, ws, &in_k1, s, false);
-        seg_scan<uint32_t>(SegN{nnz}, 1, nnz, HeadFlag{b.skeys},
-                           UniqueOut{b.skeys, b.perm, b.bag_of, b.ukeys, b.inv, b.seg_off, b.sbag,
-                                     b.scal, nnz},
-                           ws, s);
-        seg_scan<uint32_t>(SegDevN{b.scal}, 1, nnz, ChunkCount{b.seg_off, chunk},
-                           ChunkOut{b.seg_off, chunk, b.seg_chunk0, b.chunk_desc, b.multi, b.scal},
-                           ws, s);
+    if (nnz == 0) {  // only the offsets to validate and copy
+        launch_zero_i32(b.scal, 4, s);
+        if (nbags > 0)
+            hipLaunchKernelGGL(k_bags, dim3((unsigned)((nbags + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0,
+                               s, bag_off, b.bag_off, B, nnz, nbags, max_table_ids, b.bag_of,
+                               b.scal + 2);
+        else if (bag_off != b.bag_off)
+            (void)hipMemcpyAsync(b.bag_off, bag_off, sizeof(int32_t), hipMemcpyDeviceToDevice, s);
+        if (consumed) (void)hipEventRecord(consumed, s);
+        return;
     }
+    // tiles of 4096 entries, or of 1024 where a batch of them would leave most
+    // compute units idle
+    if (nnz >= SORT_LARGE)
+        launch_general<512, 8>(tb, b, ids, bag_off, B, nnz, max_table_ids, cap_u, sw, consumed, s);
+    else
+        launch_general<256, 4>(tb, b, ids, bag_off, B, nnz, max_table_ids, cap_u, sw, consumed, s);
 }
 
 }  // namespace sp

@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(BLOCK) k_backward(float4 *__restrict__ storage
     const int64_t ch = t / G;
     const int c = (int)(t % G);
     if (ch >= n_chunks) return;  // whole lane groups leave together
-    const int4 d = chunk_desc[ch];  // first position, end position, run, chunks of the run
+    const int4 d = chunk_desc[ch];  // first position, end position, run, above 1: it has more
     const int64_t p0 = d.x, p1 = d.y;
     const int32_t slot = slot_u[d.z];
     const int64_t nch = d.w;
@@ -228,7 +228,6 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
                                                        const int32_t *__restrict__ multi,
                                                        int64_t n_multi,
                                                        const int32_t *__restrict__ seg_chunk0,
-                                                       const int4 *__restrict__ chunk_desc,
                                                        const int32_t *__restrict__ slot_u,
                                                        const float4 *__restrict__ partial,
                                                        int64_t nslots, float lr)
@@ -240,7 +239,7 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
     const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
     const int32_t s = multi[m];
     const int64_t c0 = seg_chunk0[s];
-    const int64_t nch = chunk_desc[c0].w;
+    const int64_t nch = seg_chunk0[s + 1] - c0;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     int64_t q = g;
     for (; q + 3 * G < nch; q += 4 * G) {
@@ -451,7 +450,7 @@ void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,
     if (n_multi > 0)
         SP_DISPATCH_LPR_EV(D4, k_bwd_combine, dim3((unsigned)n_multi), ev[2], ev[3],
                            (float4 *)storage, (const int32_t *)b.multi, n_multi,
-                           (const int32_t *)b.seg_chunk0, (const int4 *)b.chunk_desc, slot_u,
+                           (const int32_t *)b.seg_chunk0, slot_u,
                            (const float4 *)partial, nslots, lr);
 }
 

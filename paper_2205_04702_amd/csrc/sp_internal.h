@@ -94,13 +94,14 @@ inline int ingest_splits(int T) { return T <= 16 ? 16 : (T <= 32 ? 8 : 4); }
 // One window-ring entry: a batch as it arrived plus its sort/dedup products.
 struct BatchDev {
     int32_t *ids, *bag_off, *bag_of;  // raw CSR, bag of each position
-    uint32_t *skeys, *perm;          // keys sorted ascending, position of each sorted key
+    uint32_t *perm;                  // position of each sorted key
     int32_t *sbag;                   // bag of each sorted position
     uint32_t *ukeys;                 // unique keys ascending
     int32_t *inv;                    // [nnz] index of each position's key in ukeys
-    int32_t *seg_off;                // [n_unique+1] start of each key's run in skeys
-    int32_t *seg_chunk0;             // [n_unique] first backward chunk of each run
-    int4 *chunk_desc;                // [n_chunks] first pos, end pos, run, chunks of the run
+    int32_t *seg_off;                // [n_unique+1] start of each key's run of sorted positions
+    int32_t *seg_chunk0;             // [n_unique+1] first backward chunk of each run
+    int4 *chunk_desc;                // [n_chunks] first pos, end pos, run, above 1 when the run
+                                     // has more chunks
     int32_t *multi;                  // [n_multi] runs longer than one chunk (any order)
     int32_t *scal;                   // [0] n_unique, [1] n_chunks, [2] ERR_* bits, [3] n_multi
     int32_t *eslot;                  // [n_unique] slot of each unique key when the batch
@@ -229,14 +230,29 @@ struct IngestCons {
     uint64_t *word;
     uint32_t seq;
 };
+// Workspace of the general ingest path (one per stream that runs it): two
+// buffers of entries, digit counts, and the runs' tile counts and prefixes.
+// err gathers the batch's error bits and arrived the finished blocks; both are
+// zero between ingests.
+struct SortWs {
+    uint64_t *e[2];
+    uint32_t *hist;
+    uint64_t *tcount;
+    int4 *tpre;
+    int32_t *arrived, *err;
+};
+struct SortWsSize {
+    int64_t entries;  // of both buffers together
+    int64_t hist, tiles;
+};
+SortWsSize sort_ws_size(int64_t n);  // for batches of at most n IDs
 // Ingest one batch.  In LDS (ingest_in_lds and nnz > 0) the inputs are known
 // read when *ic.word reads ic.seq; otherwise when `consumed` (if not null)
 // completes.
 void launch_ingest(const Tables &tb, const BatchDev &b, const int32_t *ids, const int32_t *bag_off,
-                   int32_t B, int64_t nnz, int key_bits, int chunk, int64_t max_table_ids,
-                   int64_t cap_u, int64_t cap_c, uint32_t *tmp_k, uint32_t *tmp_v,
-                   uint32_t *hist, ScanWs &ws, hipEvent_t consumed, const IngestCons &ic,
-                   hipStream_t s);
+                   int32_t B, int64_t nnz, int chunk, int64_t max_table_ids, int64_t cap_u,
+                   int64_t cap_c, const SortWs &sw, ScanWs &ws, hipEvent_t consumed,
+                   const IngestCons &ic, hipStream_t s);
 
 void launch_radix_sort(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t n,
                        int bits, uint32_t *hist, ScanWs &ws, bool *in_k1, hipStream_t s,
