@@ -391,9 +391,8 @@ struct sp_ctx {
     uint32_t *pf_own_key = nullptr;  // prefetch mode: the planned batch's own misses,
     int32_t *pf_own_uidx = nullptr;  // as the query compacts them
     int32_t *pf_flag = nullptr;      // [pf_depth][max_ids] successors' unique keys to prefetch
-    uint64_t *hash = nullptr;
-    uint32_t hash_mask = 0;
-    int64_t hash_used = 0;
+    HitMap map{};             // the hash or the dense map
+    int64_t hash_used = 0;    // entries of the hash in use, erased ones included
 
     // window ring: batch q lives in entry q % nring (ring_batch[r] = q, -1 if none)
     int nring = 0;
@@ -401,6 +400,7 @@ struct sp_ctx {
     std::vector<int64_t> ring_batch, ring_nnz, ring_B;
     std::vector<hipEvent_t> ring_ready;     // ingest of the entry's batch finished
     std::vector<char> ring_seen;            // the plan stream has waited for ring_ready
+    std::vector<char> ring_entered;         // an accepted plan has entered the batch: eslot holds
     hipEvent_t ev_consumed = nullptr;       // last ingest has read the caller's arrays
 
     // tickets
@@ -938,11 +938,20 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     TRY(dalloc(h, &h->pend, h->total_rows));
     TRY(dalloc(h, &h->hcnt, (int64_t)MAX_TABLES * HOLD_RING));
     if (h->policy == POLICY_LFU) TRY(dalloc(h, &h->uses, S));
+    // at least four entries per slot: the hash is cleared of erased entries
+    // when 70% are in use, so a plan's misses may reach a quarter of the slots
+    // for several plans between two rebuilds (with two entries per slot the
+    // 4x20k workload rebuilt at every plan, 17 us each)
     int64_t cap = 1024;
-    while (cap < 2 * S) cap <<= 1;
-    if (cap > (int64_t)1 << 32) return fail(nullptr, SP_ERR_INVALID_ARG, "too many slots");
-    h->hash_mask = (uint32_t)(cap - 1);
-    TRY(dalloc(h, &h->hash, cap));
+    while (cap < 4 * S) cap <<= 1;
+    if (cap > (int64_t)1 << 32) cap = (int64_t)1 << 32;
+    if (cap < 2 * S) return fail(nullptr, SP_ERR_INVALID_ARG, "too many slots");
+    if (h->total_rows * (int64_t)sizeof(int32_t) <= cap * (int64_t)sizeof(uint64_t)) {
+        TRY(dalloc(h, &h->map.dense, h->total_rows));
+    } else {
+        h->map.mask = (uint32_t)(cap - 1);
+        TRY(dalloc(h, &h->map.hash, cap));
+    }
 
     // batches k-max(1, P) (training, or held as past) .. k+L+SP_MAX_AHEAD
     // (prepared) plus one of slack
@@ -953,6 +962,7 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     h->ring_B.assign(h->nring, 0);
     h->ring_ready.assign(h->nring, nullptr);
     h->ring_seen.assign(h->nring, 0);
+    h->ring_entered.assign(h->nring, 0);
     h->tk.assign(h->nring, TicketDev{});
     h->tkh.assign(h->nring, TicketHost{});
     h->ev_planned.assign(h->nring, nullptr);
@@ -965,12 +975,10 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         TRY(dalloc(h, &b.ids, N));
         TRY(dalloc(h, &b.bag_off, TB1));
         TRY(dalloc(h, &b.bag_of, N));
-        TRY(dalloc(h, &b.perm, N));
         TRY(dalloc(h, &b.sbag, N));
         TRY(dalloc(h, &b.ukeys, N));
         TRY(dalloc(h, &b.eslot, N));
         TRY(dalloc(h, &b.inv, N));
-        TRY(dalloc(h, &b.seg_off, N + 1));
         TRY(dalloc(h, &b.seg_chunk0, N + 1));
         TRY(dalloc(h, &b.chunk_desc, nchunk_max));
         TRY(dalloc(h, &b.multi, multi_capacity(N, h->chunk)));
@@ -990,7 +998,6 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         TicketDev &t = h->tk[k];
         TRY(dalloc(h, &t.hit, N));
         TRY(dalloc(h, &t.slot_u, N));
-        TRY(dalloc(h, &t.slot_of, N));
         TRY(dalloc(h, &t.m_key, NM));
         TRY(dalloc(h, &t.m_uidx, NM));
         TRY(dalloc(h, &t.v_slot, NM));
@@ -1116,7 +1123,8 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         HIPCHK(nullptr, hipMemcpy(h->rbase, rb.data(), sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice));
     }
     HIPCHK(nullptr, hipMemsetAsync(h->hcnt, 0, sizeof(int32_t) * MAX_TABLES * HOLD_RING, h->s_plan));
-    HIPCHK(nullptr, hipMemsetAsync(h->hash, 0xFF, sizeof(uint64_t) * cap, h->s_plan));
+    if (h->map.dense) HIPCHK(nullptr, hipMemsetAsync(h->map.dense, 0xFF, sizeof(int32_t) * h->total_rows, h->s_plan));
+    else HIPCHK(nullptr, hipMemsetAsync(h->map.hash, 0xFF, sizeof(uint64_t) * cap, h->s_plan));
     // all-ones words are NaN: under SP_FLAG_POISON a read of a never-filled slot shows
     HIPCHK(nullptr, hipMemsetAsync(h->storage, h->poison ? 0xFF : 0, sizeof(float) * S * h->D, h->s_plan));
     HIPCHK(nullptr, hipMemsetAsync(h->sel_hist, 0, sizeof(int32_t) * MAX_TABLES * SEL_BINS, h->s_plan));
@@ -1337,6 +1345,7 @@ static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead,
     HIPCHK(h, hipEventRecord(h->ring_ready[r], si));
     if (timing) HIPCHK(h, h->t_ing.end(si));
     h->ring_seen[r] = 0;
+    h->ring_entered[r] = 0;
     h->ring_batch[r] = q;
     h->ring_nnz[r] = bt.nnz;
     h->ring_B[r] = bt.batch;
@@ -1556,10 +1565,12 @@ static sp_status enqueue_query(sp_ctx *h, int64_t k, int nhold, uint32_t *seq_ou
     int64_t max_nnz = 0;
     for (int w = 0; w < nwin; ++w) {
         qr.qoff[w] = w < nhold ? w : -(w - nhold + 1);
-        qr.eslot[w] = h->ring[(k + qr.qoff[w]) % h->nring].eslot;
+        const int r = (int)((k + qr.qoff[w]) % h->nring);
+        qr.eslot[w] = h->ring[r].eslot;
         th.ent_len[w] = nnz[w];
         const bool ent = qr.rebuild || (w < nhold && k + w > h->entered);
         if (ent) qr.entrant |= 1u << w;
+        else if (h->ring_entered[r]) qr.known |= 1u << w;
         if (w == 0 || w <= pf.depth || ent) {
             qr.idx[qr.n++] = w;
             max_nnz = std::max(max_nnz, nnz[w]);
@@ -1582,7 +1593,7 @@ static sp_status enqueue_query(sp_ctx *h, int64_t k, int nhold, uint32_t *seq_ou
         TRY(join_fill(h, k - h->nstage));
         host_keys = h->h_mkey_dev[sl];
     }
-    launch_query(h->tb, h->hash, h->hash_mask, th.uk, th.nu, nwin, max_nnz, h->hold_to, h->held,
+    launch_query(h->tb, h->map, th.uk, th.nu, nwin, max_nnz, h->hold_to, h->held,
                  th.stamp, h->hcnt, (int32_t)k, qr, RowIndex{h->rbase, h->lastq, h->pend}, h->tk[e],
                  pf, h->cnt, h->cnt_part,
                  h->cnt_part + PART_COPIES * PART_WORDS, h->ring[k % h->nring].scal, h->h_cnt_dev,
@@ -1697,7 +1708,6 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     }
 
     // ---- phase 2: commit
-    const BatchDev &b0 = h->ring[r0];
     th.nnz = h->ring_nnz[r0];
     th.B = (int32_t)h->ring_B[r0];
     th.n_unique = c.n_unique;
@@ -1771,6 +1781,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
         hr.nv_off[y] = th.qr.qoff[w] + h->P;
         hr.q_off[y] = th.qr.qoff[w];
         hr.start[y + 1] = hr.start[y] + th.ent_len[w];
+        h->ring_entered[(k + th.qr.qoff[w]) % h->nring] = 1;
     }
     const RowIndex ri{h->rbase, h->lastq, h->pend};
     // the filled rows' holds from lastq / pend when at most one batch enters
@@ -1782,9 +1793,9 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     }
 
     if (n_miss > 0) {
-        const int64_t cap = (int64_t)h->hash_mask + 1;
-        if (h->hash_used + n_miss > cap * 7 / 10) {
-            launch_hash_rebuild(h->hash, h->hash_mask, h->key_of_slot, h->total_slots, h->cnt, h->s_plan);
+        const int64_t cap = (int64_t)h->map.mask + 1;
+        if (h->map.hash && h->hash_used + n_miss > cap * 7 / 10) {
+            launch_hash_rebuild(h->map.hash, h->map.mask, h->key_of_slot, h->total_slots, h->cnt, h->s_plan);
             h->hash_used = h->total_slots;
             ++h->st.hash_rebuilds;
         }
@@ -1844,8 +1855,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     wk.ent = ent;
     wk.stamp = th.stamp;
     for (int w = 0; w < nhold; ++w) wk.uk[w] = th.uk[w], wk.nu[w] = th.nu[w];
-    launch_commit(h->tb, h->hash, h->hash_mask, tk, b0, n_miss, th.n_unique, th.nnz, h->key_of_slot,
-                  h->last_use, h->uses, u, pf_on, wk, hr, ri, h->hold_to, h->hcnt, h->cnt, h->s_plan);
+    launch_commit(h->tb, h->map, tk, n_miss, th.n_unique, h->key_of_slot, h->last_use, h->uses, u, pf_on, wk, hr, ri, h->hold_to, h->hcnt, h->cnt, h->s_plan);
     CHECK_LAUNCH(h);
     h->entered = th.qr.rebuild ? k + nhold - 1 : std::max(h->entered, k + nhold - 1);
     if (h->ws_plan.overflow) return fail(h, SP_ERR_HIP, "internal: scan workspace too small");
@@ -1985,7 +1995,7 @@ extern "C" sp_status sp_forward(sp_handle h, int64_t ticket, float *d_out, void 
     hipStream_t s = (hipStream_t)stream;
     // The batch's rows are resident once the fills that brought them are done:
     // this plan's, if the batch had misses of its own (its fill also follows
-    // the commit that wrote slot_of); otherwise earlier ones only (with
+    // the commit that completed slot_u); otherwise earlier ones only (with
     // prefetch the previous plan's), and the commit is waited for by itself.
     // This plan's fill writes only victim slots, which hold no row of the
     // batch, so the forward and the update then overlap it.
@@ -2012,8 +2022,8 @@ extern "C" sp_status sp_forward(sp_handle h, int64_t ticket, float *d_out, void 
         HIPCHK(h, wait_unless_done(s, h->ev_upd[(ticket - 1) % h->nring]));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if ((h->flags & SP_FLAG_TIMING) && nbags > 0) HIPCHK(h, h->t_fwd.take(&e0, &e1));
-    launch_forward(h->storage, h->D, h->total_slots, h->tk[e].slot_of, h->ring[th.ring].bag_off,
-                   nbags, d_out, s, e0, e1);
+    launch_forward(h->storage, h->D, h->total_slots, h->ring[th.ring].inv, h->tk[e].slot_u, th.n_unique,
+                   h->ring[th.ring].bag_off, nbags, d_out, s, e0, e1);
     CHECK_LAUNCH(h);
     h->forwarded = ticket + 1;
     if (h->flags & SP_FLAG_DEBUG_SYNC) HIPCHK(h, hipDeviceSynchronize());
@@ -2215,7 +2225,8 @@ extern "C" sp_status sp_debug_plan(sp_handle h, int64_t ticket, sp_plan_dump *d)
     }
     if (nnz > 0) {
         HIPCHK(h, hipMemcpy(d->inv, b.inv, sizeof(int32_t) * nnz, hipMemcpyDeviceToHost));
-        HIPCHK(h, hipMemcpy(d->slot_of, tk.slot_of, sizeof(int32_t) * nnz, hipMemcpyDeviceToHost));
+        for (int64_t j = 0; j < nnz; ++j)
+            d->slot_of[j] = d->inv[j] >= 0 && d->inv[j] < nu ? d->slot_u[d->inv[j]] : -1;
     }
     int64_t nev = 0;
     if (nm > 0) {

@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(NT) k_sort_scatter(Tables tb, const int32_t *i
 // one run at most) that start in it and the runs longer than one chunk; its
 // last block to finish turns the counts into prefixes and writes the batch's
 // totals and error bits.  k_runs<true> finds the same starts again and writes
-// everything at its place: unique keys, run offsets, chunk descriptors, and
+// everything at its place: unique keys, chunk descriptors, and
 // per sorted entry the bag (sbag) and the run of its position (inv).  The
 // second reading of the entries (8 bytes each) buys tiles that need no order
 // among them, so consecutive tiles stay on one XCD and the scattered stores of
@@ -562,7 +562,6 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
             b.scal[1] = C;
             b.scal[2] = atomicExch(err, 0);
             b.scal[3] = (int32_t)tot_m;
-            b.seg_off[U] = (int32_t)total;
             b.seg_chunk0[U] = C;
             __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -581,7 +580,6 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
         const uint32_t kk = key[1 + i];
         if (head) {
             b.ukeys[u] = kk;
-            b.seg_off[u] = (int32_t)(base + i);
             b.seg_chunk0[u] = c;
             if (lng && m < n_multi_cap) b.multi[m] = u;
             m += lng;
@@ -604,7 +602,6 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
         if (i >= n) continue;
         const uint32_t p = pos[i];
         if (p >= (uint64_t)nnz) continue;
-        b.perm[base + i] = p;
         b.sbag[base + i] = bag_of[p];
         b.inv[p] = (int32_t)seg[i];
     }
@@ -1124,13 +1121,9 @@ __global__ void __launch_bounds__(IG_THREADS) k_ingest_table(Tables tb, const in
         const int64_t pos = j0 + (int64_t)(e[q] & IG_LOW);
         const int64_t gi = jb + i;
         if ((heads >> q) & 1u) {
-            if ((int64_t)U0 + sg < cap_u) {
-                b.ukeys[U0 + sg] = ((uint32_t)t << rb) | row;
-                b.seg_off[U0 + sg] = (int32_t)gi;
-            }
+            if ((int64_t)U0 + sg < cap_u) b.ukeys[U0 + sg] = ((uint32_t)t << rb) | row;
             ++sg;
         }
-        b.perm[gi] = (uint32_t)pos;
         b.sbag[gi] = (int32_t)((int64_t)t * B + bag);
         b.inv[pos] = (int32_t)(U0 + sg - 1);
     }
@@ -1157,10 +1150,7 @@ __global__ void __launch_bounds__(IG_THREADS) k_ingest_table(Tables tb, const in
     }
     if (id == (uint32_t)(tb.T * S - 1) && tid == 0) {  // the batch totals
         const uint32_t U = U0 + nU;
-        if ((int64_t)U < cap_u + 1) {
-            b.seg_off[U] = (int32_t)nnz;
-            b.seg_chunk0[U] = (int32_t)(C0 + nC);
-        }
+        if ((int64_t)U < cap_u + 1) b.seg_chunk0[U] = (int32_t)(C0 + nC);
         b.scal[0] = (int32_t)U;
         b.scal[1] = (int32_t)(C0 + nC);
         b.scal[2] = (int32_t)(before_s[3] | (uint32_t)err_s);
@@ -1197,8 +1187,8 @@ static void launch_general(const Tables &tb, const BatchDev &b, const int32_t *i
     }
     const int64_t flat = (nnz + TILE - 1) / TILE;
     const int64_t tiles = flat + tb.T;  // at least those of all tables, whatever their spans
-    int G = 1;  // near the square root of a table's tiles
-    while (G < 32 && (int64_t)G * G * tb.T < flat) G *= 2;
+    int G = 1;  // near the square root of a table's tiles, with blocks for every compute unit
+    while (G < 32 && (int64_t)G * G * tb.T < flat && flat / G > 1024) G *= 2;
     const int64_t groups = flat / G + tb.T + 1;
     uint32_t *const thist = sw.hist, *const ghist = sw.hist + tiles * SORT_BINS;
     const int64_t bag_blocks = (nbags + NT - 1) / NT;

@@ -10,7 +10,7 @@ namespace sp {
 
 // ---------------------------------------------------------------- query + hold
 
-static_assert(QUERY_TILE == BLOCK, "one unique key per query thread");
+static_assert(QUERY_TILE == BLOCK, "at least one unique key per query thread");
 
 struct ProbeArgs {
     const uint32_t *uk[MAX_WINDOW];
@@ -34,20 +34,30 @@ __device__ __forceinline__ P pick_uniform(const P (&a)[MAX_WINDOW], int w)
 // (the planned one) records hit / slot, counts misses and compacts them in
 // ascending key order into m_key / m_uidx with a single-pass scan (its blocks
 // take their tiles of keys from an atomic counter, so a tile only looks back
-// at tiles whose blocks have started).  A batch entering the hold window
-// records the slot of each of its keys (eslot) and stamps each cached slot
-// with this query's stamp (held[slot] = stamp, which the victim choice of
-// this plan treats as held); the first stamp of a slot counts it, per table,
-// when hold_to < plan: the slots the plan newly holds.  An uncached key of
-// such a batch writes the stamp to its row's pend entry, which tells this
-// plan's commit that the key is in the entering batch.  hold_to is not
-// written here, so a rejected plan changes nothing (its stamp is never
-// matched again); the commit raises it.  Held slots at this plan are those
-// newly held plus those whose hold_to lies in plan .. plan + span - 1,
-// counted in hcnt.  Per-table counts are summed
-// across the wave (keys are sorted, so a wave nearly always covers one table),
-// then across the block in LDS, then added to one of PART_COPIES copies of the
-// counters so that few blocks contend for an address.
+// at tiles whose blocks have started).  A batch that entered the window at an
+// earlier plan has its slots as of then in eslot; those rows have been held
+// since, so only the keys without a slot are looked up again.  A batch
+// entering the hold window records the slot of each of its keys (eslot) and
+// stamps each cached slot with this query's stamp (held[slot] = stamp, which
+// the victim choice of this plan treats as held); the first stamp of a slot
+// counts it, per table, when hold_to < plan: the slots the plan newly holds.
+// One batch's unique keys have a slot each, so with a single entering batch
+// (every plan but the first ones and rebuilds) stamps are plain stores; with
+// several, exchanges tell the first.  An uncached key of such a batch writes
+// the stamp to its row's pend entry, which tells this plan's commit that the
+// key is in the entering batch.  hold_to is not written here, so a rejected
+// plan changes nothing (its stamp is never matched again); the commit raises
+// it.  Held slots at this plan are those newly held plus those whose hold_to
+// lies in plan .. plan + span - 1, counted in hcnt.  Per-table counts are
+// summed across the wave (keys are sorted, so a wave nearly always covers one
+// table), then across the block in LDS, then added to one of `copies` copies
+// of the counters so that few blocks contend for an address.
+//
+// What bounds it: the chain of dependent accesses when small; when large,
+// random accesses and, before, device-scope atomics (one exchange per entering
+// key, three on one address per block of 256 keys): KPT keys per thread then
+// cut the blocks.  2.1M unique keys a batch: 2.24 ms before, QUERY_MS_MIXED
+// now; 1.05M: 0.58 ms before, QUERY_MS_26 now.
 //
 // Every add a block makes returns its old value, and each thread tests the
 // values before the block's barrier, so all of a block's adds have been
@@ -77,107 +87,180 @@ __device__ __forceinline__ bool in_sorted(const uint32_t *__restrict__ a, int32_
     return lo < n && a[lo] == key;
 }
 
-__global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T,
-                                                 const uint64_t *__restrict__ hash, uint32_t mask,
+template <int KPT>
+__global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T, HitMap map,
                                                  ProbeArgs pa, PrefetchDev pf,
                                                  const int32_t *__restrict__ hold_to,
                                                  int32_t *held, int32_t stamp,
                                                  int32_t *hcnt, int32_t plan, QueryRows qr,
                                                  RowIndex ri,
                                                  int32_t *hit, int32_t *slot_u, DevCounters *cnt,
-                                                 int32_t *part, int32_t *arrived,
+                                                 int32_t *part, int32_t copies, int32_t *arrived,
                                                  const int32_t *scal0, uint64_t *host_mapped,
                                                  uint32_t seq, uint32_t *m_key, int32_t *m_uidx,
                                                  uint32_t *host_keys, int64_t host_cap, ScanDev d)
 {
+    constexpr int WAVES = BLOCK / WAVE;
     __shared__ int32_t c_miss[MAX_TABLES], c_held[MAX_TABLES], c_pf[MAX_TABLES];  // c_pf: row w's
     __shared__ int32_t last_s;
     __shared__ uint32_t tile_s, pref_s;
-    __shared__ uint32_t lds_scan[BLOCK / WAVE];
+    __shared__ uint32_t missed[KPT * WAVES];  // misses of each (round, wave)
     const int w = pick_uniform(qr.idx, (int)blockIdx.y);
     const bool entrant = (qr.entrant >> w) & 1u;
+    const bool known = (qr.known >> w) & 1u;
+    const bool one_entrant = (qr.entrant & (qr.entrant - 1u)) == 0;
+    // the grid covers a batch of only unique IDs; blocks past the row's keys
+    // leave at once and are not counted below
+    const int32_t *const nuw = pick_uniform(pa.nu, w);
+    const int64_t n = *nuw;
+    auto row_tiles = [](int64_t keys) {
+        return keys > BLOCK * KPT ? (keys + BLOCK * KPT - 1) / (BLOCK * KPT) : (int64_t)1;
+    };
+    const int64_t tiles = row_tiles(n);
+    if (blockIdx.x >= tiles) return;
     for (int t = threadIdx.x; t < T; t += BLOCK) c_miss[t] = c_held[t] = c_pf[t] = 0;
-    if (w == 0 && threadIdx.x == 0) tile_s = atomicAdd(d.counter, 1u) - d.base;
+    int32_t blocks = 0;  // that arrive
+    if (threadIdx.x == 0) {
+        if (w == 0) tile_s = atomicAdd(d.counter, 1u) - d.base;
+        for (int y = 0; y < qr.n; ++y) blocks += (int32_t)row_tiles(*pa.nu[qr.idx[y]]);
+    }
     __syncthreads();
-    const int64_t xb = w == 0 ? (int64_t)tile_s : (int64_t)blockIdx.x;
+    // the planned batch's tiles go by the counter; another row's consecutive
+    // tiles (one table's) to one XCD
+    const int64_t xb = w == 0 ? (int64_t)tile_s : xcd_block(blockIdx.x, tiles);
     if (xb >= (int64_t)gridDim.x) {  // the counter and the host disagree: give up loudly
         if (threadIdx.x == 0) atomicOr(d.err, ERR_PLAN);
         return;
     }
-    const int64_t i = xb * BLOCK + threadIdx.x;
+    const int64_t i0 = xb * (BLOCK * KPT) + threadIdx.x;
     int32_t seen = 0;  // returned old values; tested below so the adds complete first
-    if (w == 0 && i == 0) {
+    if (w == 0 && i0 == 0) {
         seen |= atomicExch(&cnt->n_unique, scal0[0]) == INT32_MIN;
         seen |= atomicExch(&cnt->n_chunks, scal0[1]) == INT32_MIN;
         seen |= atomicExch(&cnt->n_multi, scal0[3]) == INT32_MIN;
     }
     const uint32_t *const ukw = pick_uniform(pa.uk, w);
-    const int32_t *const nuw = pick_uniform(pa.nu, w);
-    if (i == 0 && nuw[2]) seen |= atomicOr(&cnt->err, nuw[2]) == INT32_MIN;
-    const bool valid = i < *nuw;
-    int t = 0;
-    bool miss = false, fresh = false, fetch = false;
-    uint32_t key = 0;
-    if (valid) {
-        key = ukw[i];
-        t = (int)(key >> row_bits);
-        const int32_t slot = hash_find_ro(hash, mask, key);  // the map is not written here
-        if (w == 0) {
-            hit[i] = slot >= 0;
-            slot_u[i] = slot;
-            miss = slot < 0;
+    int32_t *const esw = pick_uniform(qr.eslot, w);
+    if (i0 == 0 && nuw[2]) seen |= atomicOr(&cnt->err, nuw[2]) == INT32_MIN;
+    // keys, what is known of their slots, then the lookups: each round of
+    // loads is in flight for all of the thread's keys
+    uint32_t key[KPT];
+    int32_t slot[KPT];
+    int64_t row[KPT];
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int64_t i = i0 + r * BLOCK;
+        key[r] = i < n ? ukw[i] : 0u;
+        slot[r] = known && i < n ? esw[i] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int t = (int)(key[r] >> row_bits);
+        row[r] = ri.rbase[t < T ? t : 0] + (key[r] & ((1u << row_bits) - 1u));
+    }
+#pragma unroll
+    for (int r = 0; r < KPT; ++r)
+        if (i0 + r * BLOCK < n && slot[r] < 0) slot[r] = map_find_ro(map, key[r], row[r]);
+    uint32_t missbits = 0, freshbits = 0, fetchbits = 0, rank[KPT];
+    if (entrant) {
+        int32_t ht[KPT];
+#pragma unroll
+        for (int r = 0; r < KPT; ++r)
+            ht[r] = slot[r] >= 0 && i0 + r * BLOCK < n ? hold_to[slot[r]] : plan;
+#pragma unroll
+        for (int r = 0; r < KPT; ++r) {
+            const int64_t i = i0 + r * BLOCK;
+            if (i >= n) continue;
+            bool fresh = false;
+            if (slot[r] >= 0) {
+                fresh = qr.rebuild || ht[r] < plan;
+                if (one_entrant)
+                    held[slot[r]] = stamp;
+                else
+                    fresh = atomicExch(&held[slot[r]], stamp) != stamp && fresh;
+            } else if ((int)(key[r] >> row_bits) < T) {
+                ri.pend[row[r]] = stamp;
+            }
+            freshbits |= (uint32_t)fresh << r;
+            esw[i] = slot[r];
         }
-        if (entrant) {
-            if (slot >= 0)
-                fresh = atomicExch(&held[slot], stamp) != stamp &&
-                        (qr.rebuild || hold_to[slot] < plan);
-            else if (t < T)
-                ri.pend[ri.rbase[t] + (key & ((1u << row_bits) - 1u))] = stamp;
-            pick_uniform(qr.eslot, w)[i] = slot;
-        }
-        if (w >= 1 && w <= pf.depth) {
-            fetch = slot < 0;
+    }
+    if (w >= 1 && w <= pf.depth) {
+#pragma unroll
+        for (int r = 0; r < KPT; ++r) {
+            const int64_t i = i0 + r * BLOCK;
+            if (i >= n) continue;
+            bool fetch = slot[r] < 0;
 #pragma unroll
             for (int e = 0; e < MAX_PF; ++e)  // the earlier batches 0 .. w-1
-                if (e < w && fetch) fetch = !in_sorted(pa.uk[e], *pa.nu[e], key);
+                if (e < w && fetch) fetch = !in_sorted(pa.uk[e], *pa.nu[e], key[r]);
             pf.flag[(int64_t)(w - 1) * pf.stride + i] = fetch;
+            fetchbits |= (uint32_t)fetch << r;
         }
     }
-    if (w == 0 && xb * BLOCK < (int64_t)*pa.nu[0]) {  // uniform per block
-        uint32_t tot;
-        const uint32_t ex = block_excl_scan((uint32_t)miss, lds_scan, tot);
+    if (w == 0) {
+#pragma unroll
+        for (int r = 0; r < KPT; ++r) {
+            const int64_t i = i0 + r * BLOCK;
+            const bool miss = i < n && slot[r] < 0;
+            if (i < n) {
+                hit[i] = slot[r] >= 0;
+                slot_u[i] = slot[r];
+            }
+            const uint64_t bal = __ballot(miss);
+            missbits |= (uint32_t)miss << r;
+            rank[r] = (uint32_t)__popcll(bal & lanemask_lt());
+            if (lane_id() == 0) missed[r * WAVES + wave_id()] = (uint32_t)__popcll(bal);
+        }
+    }
+    if (w == 0 && xb * (BLOCK * KPT) < n) {  // uniform per block
+        __syncthreads();
         if (threadIdx.x < WAVE) {
+            static_assert(KPT * WAVES <= WAVE, "one count per lane");
+            const int lane = lane_id();
+            const uint32_t c = lane < KPT * WAVES ? missed[lane] : 0u;
+            const uint32_t incl = wave_incl_scan(c);
+            if (lane < KPT * WAVES) missed[lane] = incl - c;
+            const uint32_t tot = __shfl(incl, WAVE - 1, WAVE);
             const uint32_t pre = lb_lookback<uint32_t>(d, (uint32_t)xb, (int)xb, tot);
-            if (threadIdx.x == 0) pref_s = pre;
+            if (lane == 0) pref_s = pre;
         }
         __syncthreads();
-        if (miss) {
-            uint32_t *const mk = pf.depth > 0 ? pf.own_key : m_key;
-            int32_t *const mu = pf.depth > 0 ? pf.own_uidx : m_uidx;
-            mk[pref_s + ex] = key;
-            mu[pref_s + ex] = (int32_t)i;
+        uint32_t *const mk = pf.depth > 0 ? pf.own_key : m_key;
+        int32_t *const mu = pf.depth > 0 ? pf.own_uidx : m_uidx;
+#pragma unroll
+        for (int r = 0; r < KPT; ++r) {
+            if (!((missbits >> r) & 1u)) continue;
+            const uint32_t at = pref_s + missed[r * WAVES + wave_id()] + rank[r];
+            mk[at] = key[r];
+            mu[at] = (int32_t)(i0 + r * BLOCK);
             // the staged fill's host threads read the misses from pinned memory
-            if (host_keys && pref_s + ex < (uint64_t)host_cap) host_keys[pref_s + ex] = key;
+            if (host_keys && at < (uint64_t)host_cap) host_keys[at] = key[r];
         }
     }
-    uint64_t todo = __ballot(valid);
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const int tl = __shfl(t, leader, WAVE);
-        const bool mine = valid && t == tl;
-        const uint64_t same = __ballot(mine);
-        const int nm = __popcll(__ballot(mine && miss));
-        const int nh = __popcll(__ballot(mine && fresh));
-        const int nf = __popcll(__ballot(mine && fetch));
-        if (lane_id() == leader) {
-            if (nm) atomicAdd(&c_miss[tl], nm);
-            if (nh) atomicAdd(&c_held[tl], nh);
-            if (nf) atomicAdd(&c_pf[tl], nf);
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const bool counted = ((missbits | freshbits | fetchbits) >> r) & 1u;
+        const int t = (int)(key[r] >> row_bits);
+        uint64_t todo = __ballot(counted);
+        while (todo) {
+            const int leader = __ffsll((unsigned long long)todo) - 1;
+            const int tl = __shfl(t, leader, WAVE);
+            const bool mine = counted && t == tl;
+            const uint64_t same = __ballot(mine);
+            const int nm = __popcll(__ballot(mine && ((missbits >> r) & 1u)));
+            const int nh = __popcll(__ballot(mine && ((freshbits >> r) & 1u)));
+            const int nf = __popcll(__ballot(mine && ((fetchbits >> r) & 1u)));
+            if (lane_id() == leader && tl < T) {
+                if (nm) atomicAdd(&c_miss[tl], nm);
+                if (nh) atomicAdd(&c_held[tl], nh);
+                if (nf) atomicAdd(&c_pf[tl], nf);
+            }
+            todo &= ~same;
         }
-        todo &= ~same;
     }
     __syncthreads();
-    int32_t *p = part + (int64_t)((blockIdx.y * gridDim.x + blockIdx.x) % PART_COPIES) * PART_WORDS;
+    int32_t *p = part + (int64_t)((blockIdx.y * gridDim.x + blockIdx.x) % copies) * PART_WORDS;
     const int pfw = w >= 1 && w <= MAX_PF ? w - 1 : 0;  // this row's prefetch counts
     for (int tt = threadIdx.x; tt < T; tt += BLOCK) {
         if (c_miss[tt]) seen |= atomicAdd(&p[tt], c_miss[tt]);
@@ -187,7 +270,7 @@ __global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T,
     if (seen < 0) cnt->pad2[0] = seen;  // never taken (counts are not negative)
     __syncthreads();
     if (threadIdx.x == 0)
-        last_s = atomicAdd(arrived, 1) == (int32_t)(gridDim.x * gridDim.y) - 1;
+        last_s = atomicAdd(arrived, 1) == blocks - 1;
     __syncthreads();
     if (!last_s) return;  // uniform per block
 
@@ -196,7 +279,7 @@ __global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T,
     for (int j = threadIdx.x; j < PART_WORDS; j += BLOCK) sums[j] = 0;
     __syncthreads();
     const int na = 2 + pf.depth;  // live arrays per copy: miss, held, one per successor
-    const int n_rel = PART_COPIES * na * T;
+    const int n_rel = copies * na * T;
     auto word = [T, na](int r) {  // the r-th live word: copy c, array a, table
         const int c = r / (na * T), jj = r % (na * T), a = jj / T;
         return c * PART_WORDS + a * MAX_TABLES + (jj - a * T);
@@ -236,10 +319,19 @@ __global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T,
     for (int t = threadIdx.x; t < T; t += BLOCK)
         __hip_atomic_store(&hcnt[t * HOLD_RING + ((plan + qr.span) & (HOLD_RING - 1))], 0,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (threadIdx.x == 0) __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the next launch counts from a whole row of tiles on
+        __hip_atomic_store(d.counter, d.base + d.grid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
-void launch_query(const Tables &tb, const uint64_t *hash, uint32_t mask,
+// IDs of the longest row from which a thread takes four keys, and eight.  Few
+// blocks contend less for the counters, many hide more of the chain: with one
+// key per thread 231k unique keys took 0.167 ms, 30k 13 us.
+constexpr int64_t QUERY_FOUR = 96 << 10, QUERY_EIGHT = 1 << 20;
+
+void launch_query(const Tables &tb, const HitMap &map,
                   const uint32_t *const *ukeys, const int32_t *const *nuniq, int nwin,
                   int64_t max_unique, const int32_t *hold_to, int32_t *held, int32_t stamp,
                   int32_t *hcnt, int32_t plan, const QueryRows &qr, const RowIndex &ri,
@@ -262,7 +354,9 @@ void launch_query(const Tables &tb, const uint64_t *hash, uint32_t mask,
     for (int w = 0; w < nwin; ++w) pa.uk[w] = ukeys[w], pa.nu[w] = nuniq[w];
     // at least one block per batch so that every batch's error word is read
     const int64_t n = max_unique > 0 ? max_unique : 1;
-    const int64_t gx = (n + BLOCK - 1) / BLOCK;
+    const int kpt = n >= QUERY_EIGHT ? 8 : (n >= QUERY_FOUR ? 4 : 1);
+    const int64_t gx = (n + BLOCK * kpt - 1) / (BLOCK * kpt);
+    const int copies = gx * qr.n > 256 ? PART_COPIES : PART_COPIES / 4;
     if (gx > ws.max_tiles) {
         ws.overflow = true;
         return;
@@ -273,11 +367,16 @@ void launch_query(const Tables &tb, const uint64_t *hash, uint32_t mask,
     }
     ScanDev d{ws.status, ws.counter, ws.err, ws.issued, ++ws.epoch, (uint32_t)gx, (int32_t)gx};
     ws.issued += (uint32_t)gx;  // the planned batch's row of blocks takes tiles
-    hipLaunchKernelGGL(k_query, dim3((unsigned)gx, (unsigned)qr.n), dim3(BLOCK), 0, s, tb.row_bits,
-                       tb.T, hash, mask, pa, pf, hold_to, held, stamp, hcnt, plan, qr, ri, tk.hit,
-                       tk.slot_u, cnt,
-                       part, arrived, scal0, host_mapped, seq, tk.m_key, tk.m_uidx, host_keys,
-                       host_cap, d);
+    const dim3 grid((unsigned)gx, (unsigned)qr.n);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, s, tb.row_bits, tb.T, map, pa, pf, hold_to,
+                           held, stamp, hcnt, plan, qr, ri, tk.hit, tk.slot_u, cnt, part, copies,
+                           arrived, scal0, host_mapped, seq, tk.m_key, tk.m_uidx, host_keys,
+                           host_cap, d);
+    };
+    if (kpt == 8) launch(k_query<8>);
+    else if (kpt == 4) launch(k_query<4>);
+    else launch(k_query<1>);
 }
 
 // ---------------------------------------------------------------- holds
@@ -318,27 +417,65 @@ __device__ __forceinline__ HoldRef hold_ref(const HoldRows &hr, int64_t j)
 // batch (+ hold_past): hold_to rises to that value and, if it rose, the count
 // moves from the old value (if still live) to the new one.  Keys of two
 // entering batches may share a slot: atomicMax orders the raises, and each
-// raise moves the count exactly once.  A key not cached records the batch in
-// lastq.
-__device__ __forceinline__ void hold_key(const HoldRef &h, int32_t row_bits, int32_t T,
-                                         const RowIndex &ri, int32_t *hold_to, int32_t plan,
-                                         int32_t *c)
+// raise moves the count exactly once.  With ONE entering batch every slot has
+// one key, and plain accesses do: `old` is then what the caller loaded.  A key
+// not cached records the batch in lastq.  row: the key's RowIndex place.
+template <bool ONE>
+__device__ __forceinline__ void hold_key(int t, int32_t slot, int64_t row, int32_t old, int off,
+                                         int qo, const RowIndex &ri, int32_t *hold_to,
+                                         int32_t plan, int32_t *c)
 {
-    if (h.i >= *h.nu) return;
-    const int32_t slot = h.es[h.i];
-    const uint32_t key = h.uk[h.i];
-    const int t = (int)(key >> row_bits);
-    if (t >= T) return;
     if (slot < 0) {
-        atomicMax(&ri.lastq[ri.rbase[t] + (key & ((1u << row_bits) - 1u))], plan + h.qo);
+        if (!ONE) atomicMax(&ri.lastq[row], plan + qo);
+        else if (old < plan + qo) ri.lastq[row] = plan + qo;
         return;
     }
-    if (h.off < 0 || h.off >= HOLD_SPAN) return;
-    const int32_t old = atomicMax(&hold_to[slot], plan + h.off);
-    if (old < plan + h.off) {
+    if (off < 0 || off >= HOLD_SPAN) return;
+    if (!ONE) old = atomicMax(&hold_to[slot], plan + off);
+    else if (old < plan + off) hold_to[slot] = plan + off;
+    if (old < plan + off) {
         if (old >= plan) atomicSub(&c[t * HOLD_SPAN + (old - plan)], 1);
-        atomicAdd(&c[t * HOLD_SPAN + h.off], 1);
+        atomicAdd(&c[t * HOLD_SPAN + off], 1);
     }
+}
+
+// KPT keys of the entering batches, j0, j0 + BLOCK, ... of their sections; each
+// round of loads is in flight for all of them.
+template <int KPT, bool ONE>
+__device__ __forceinline__ void hold_keys(const HoldRows &hr, int64_t j0, int32_t row_bits,
+                                          int32_t T, const RowIndex &ri, int32_t *hold_to,
+                                          int32_t plan, int32_t *c)
+{
+    const int64_t end = hr.start[hr.n];
+    uint32_t key[KPT];
+    int32_t slot[KPT], old[KPT], off[KPT], qo[KPT];
+    int64_t row[KPT];
+    bool in[KPT];
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int64_t j = j0 + r * BLOCK;
+        const HoldRef h = hold_ref(hr, j >= 0 && j < end ? j : 0);
+        in[r] = j >= 0 && j < end && h.i < *h.nu;
+        key[r] = in[r] ? h.uk[h.i] : 0u;
+        slot[r] = in[r] ? h.es[h.i] : -1;
+        off[r] = h.off;
+        qo[r] = h.qo;
+    }
+#pragma unroll
+    for (int r = 0; r < KPT; ++r) {
+        const int t = (int)(key[r] >> row_bits);
+        in[r] = in[r] && t < T;
+        row[r] = ri.rbase[t < T ? t : 0] + (key[r] & ((1u << row_bits) - 1u));
+    }
+    if (ONE)
+#pragma unroll
+        for (int r = 0; r < KPT; ++r)
+            old[r] = !in[r] ? 0 : (slot[r] >= 0 ? hold_to[slot[r]] : ri.lastq[row[r]]);
+#pragma unroll
+    for (int r = 0; r < KPT; ++r)
+        if (in[r])
+            hold_key<ONE>((int)(key[r] >> row_bits), slot[r], row[r], ONE ? old[r] : 0, off[r],
+                          qo[r], ri, hold_to, plan, c);
 }
 
 __global__ void __launch_bounds__(BLOCK) k_hold(HoldRows hr, int32_t row_bits, int32_t T,
@@ -349,7 +486,7 @@ __global__ void __launch_bounds__(BLOCK) k_hold(HoldRows hr, int32_t row_bits, i
     for (int x = threadIdx.x; x < MAX_TABLES * HOLD_SPAN; x += BLOCK) c[x] = 0;
     __syncthreads();
     const int64_t j = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (j < hr.start[hr.n]) hold_key(hold_ref(hr, j), row_bits, T, ri, hold_to, plan, c);
+    hold_keys<1, false>(hr, j, row_bits, T, ri, hold_to, plan, c);
     __syncthreads();
     hold_counts_flush(c, hcnt, plan);
 }
@@ -679,25 +816,25 @@ void launch_select_victims(const SelArgs &a, int levels, int64_t maxS, const int
 
 // ---------------------------------------------------------------- commit
 
-// Threads [0, n_miss): miss i goes to victim slot v = v_slot[i]: record the
+// Items [0, n_miss): miss i goes to victim slot v = v_slot[i]: record the
 // slot's previous occupant and its last use, erase that key from the Hit-Map,
 // enter the new key, then touch the slot (last_use = u; with use counts, the
-// new row's count starts at this plan's use) and point every position of the
-// key at it.  Erases and inserts may interleave across
-// threads: inserts only claim EMPTY or erased entries, so they never disturb
-// a live key another thread is erasing, and the keys inserted are known to be
-// absent.  Threads [n_miss, n_miss + max(n_unique, nnz)): touch the slots of
-// hits and point the positions of hit keys at them.  Victims are unheld and
-// hits are held, so the two groups never share a slot.  A placed row is held
-// through the last window batch that has its key (binary searches of the
-// later batches' sorted keys), plus hold_past; its slot was unheld, so only
-// the new value is counted.
-__device__ __forceinline__ bool commit_fill(int64_t i, uint64_t *hash, uint32_t mask,
-                                            const TicketDev &tk, const int32_t *seg_off,
-                                            const uint32_t *perm, int64_t n_unique, int64_t nnz,
-                                            int64_t nslots, int32_t *key_of_slot,
-                                            int32_t *last_use, int32_t *uses, int32_t u,
-                                            int32_t prefetch, int32_t *err)
+// new row's count starts at this plan's use) and complete slot_u.  Erases and
+// inserts may interleave across threads: the keys inserted are known to be
+// absent, so in the dense map the two never meet, and in the hash inserts only
+// claim EMPTY or erased entries, so they never disturb a live key another
+// thread is erasing.  Items [n_miss, n_miss + n_unique): touch the slots of
+// hits.  Victims are unheld and hits are held, so the two groups never share a
+// slot.  A placed row is held through the last window batch that has its key
+// (binary searches of the later batches' sorted keys), plus hold_past; its
+// slot was unheld, so only the new value is counted.  Items from ent0: the
+// entering batches' keys (hold_key).
+__device__ __forceinline__ bool commit_fill(int64_t i, const HitMap &map, const TicketDev &tk,
+                                            const RowIndex &ri, int32_t row_bits, int32_t T,
+                                            int64_t n_unique, int64_t nslots,
+                                            int32_t *key_of_slot, int32_t *last_use,
+                                            int32_t *uses, int32_t u, int32_t prefetch,
+                                            int32_t *err)
 {
     // independent loads first: later stores could alias them, so the
     // compiler would otherwise keep each behind the stores before it
@@ -706,7 +843,8 @@ __device__ __forceinline__ bool commit_fill(int64_t i, uint64_t *hash, uint32_t 
     const uint32_t key = tk.m_key[i];
     // a prefetched row (prefetch mode, m_uidx = -1) is placed but not used
     const bool fetched = prefetch && ui == -1;
-    if ((uint32_t)v >= (uint64_t)nslots || (!fetched && (uint32_t)ui >= (uint64_t)n_unique)) {
+    if ((uint32_t)v >= (uint64_t)nslots || (!fetched && (uint32_t)ui >= (uint64_t)n_unique) ||
+        (int)(key >> row_bits) >= T) {
         atomicOr(err, ERR_PLAN);
         tk.v_old_key[i] = -1;
         tk.v_old_lu[i] = -1;
@@ -714,20 +852,20 @@ __device__ __forceinline__ bool commit_fill(int64_t i, uint64_t *hash, uint32_t 
     }
     const int32_t old = key_of_slot[v];
     const int32_t old_lu = last_use[v];
-    const int32_t p0 = fetched ? 0 : seg_off[ui], p1 = fetched ? 0 : seg_off[ui + 1];
     tk.v_old_key[i] = old;
     tk.v_old_lu[i] = old_lu;
-    if (old >= 0) hash_erase(hash, mask, (uint32_t)old);
+    if (map.dense) {
+        const uint32_t rmask = (1u << row_bits) - 1u;
+        if (old >= 0) map.dense[ri.rbase[old >> row_bits] + (old & rmask)] = -1;
+        map.dense[ri.rbase[key >> row_bits] + (key & rmask)] = v;
+    } else {
+        if (old >= 0) hash_erase(map.hash, map.mask, (uint32_t)old);
+        if (!hash_insert(map.hash, map.mask, key, v)) atomicOr(err, ERR_HASH_FULL);
+    }
     key_of_slot[v] = (int32_t)key;
-    if (!hash_insert(hash, mask, key, v)) atomicOr(err, ERR_HASH_FULL);
     last_use[v] = u;
     if (uses) uses[v] = fetched ? 0 : 1;
-    if (fetched) return true;
-    tk.slot_u[ui] = v;
-    for (int32_t p = p0; p < p1; ++p) {
-        const uint32_t j = perm[p];
-        if (j < (uint64_t)nnz) tk.slot_of[j] = v;
-    }
+    if (!fetched) tk.slot_u[ui] = v;
     return true;
 }
 
@@ -761,10 +899,16 @@ __device__ __forceinline__ int32_t last_batch_with(const WindowKeys &wk, uint32_
     return q;
 }
 
-__global__ void __launch_bounds__(BLOCK) k_commit(uint64_t *hash, uint32_t mask, TicketDev tk,
-                                                  const int32_t *inv, const int32_t *seg_off,
-                                                  const uint32_t *perm, int64_t n_miss,
-                                                  int64_t n_unique, int64_t nnz, int64_t nslots,
+// KPT items per thread: blocks clear and flush 1024 hold counters each, so
+// many keys per block pay once there are enough blocks; ONE: at most one
+// entering batch.  Bound by random 4-byte accesses (last_use of the hits,
+// hold_to of the entering keys) when large, by the chain of a fill when small.
+// 2.1M unique keys a batch: 1.03 ms while it also wrote a slot per position and
+// raised hold_to by atomics, COMMIT_MS now.
+constexpr int64_t COMMIT_FOUR = 512 << 10;  // items from which a thread takes four
+template <int KPT, bool ONE>
+__global__ void __launch_bounds__(BLOCK) k_commit(HitMap map, TicketDev tk, int64_t n_miss,
+                                                  int64_t n_unique, int64_t nslots,
                                                   int32_t *key_of_slot, int32_t *last_use,
                                                   int32_t *uses, int32_t u, int32_t prefetch,
                                                   WindowKeys wk, HoldRows hr, RowIndex ri,
@@ -773,53 +917,61 @@ __global__ void __launch_bounds__(BLOCK) k_commit(uint64_t *hash, uint32_t mask,
                                                   int32_t *err)
 {
     __shared__ int32_t c[MAX_TABLES * HOLD_SPAN];
+    // consecutive items (one table's) on one XCD
+    const int64_t b0 = xcd_block(blockIdx.x, gridDim.x) * (BLOCK * KPT);
+    if (b0 >= ent0) {  // past the keys of its entering batch (sections are as long as the IDs)
+        const HoldRef a = hold_ref(hr, b0 - ent0), z = hold_ref(hr, b0 - ent0 + BLOCK * KPT - 1);
+        if (a.uk == z.uk && a.i >= *a.nu) return;
+    }
     // blocks that move hold counts (uniform per block): fills, entering keys
-    const int64_t b0 = (int64_t)blockIdx.x * BLOCK;
-    const bool fills = b0 < n_miss || b0 + BLOCK > ent0;
+    const bool fills = b0 < n_miss || b0 + BLOCK * KPT > ent0;
     if (fills) {
         for (int x = threadIdx.x; x < MAX_TABLES * HOLD_SPAN; x += BLOCK) c[x] = 0;
         __syncthreads();
     }
-    const int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-    if (t < n_miss) {
-        if (commit_fill(t, hash, mask, tk, seg_off, perm, n_unique, nnz, nslots, key_of_slot,
-                        last_use, uses, u, prefetch, err)) {
-            const uint32_t key = tk.m_key[t];
-            const int32_t v = tk.v_slot[t];
-            const int tt = (int)(key >> row_bits);
-            int32_t q = 0;  // the last window batch with the key
-            if (wk.fast && tt < T) {
-                const int64_t row = ri.rbase[tt] + (key & ((1u << row_bits) - 1u));
-                const int32_t lq = ri.lastq[row], pd = ri.pend[row];
-                if (lq > plan + wk.n - 1) {  // from a window since shortened
-                    q = last_batch_with(wk, key);
+    if (b0 + BLOCK * KPT > ent0 && hr.n > 0)  // entering keys (items before them: j < 0)
+        hold_keys<KPT, ONE>(hr, b0 + threadIdx.x - ent0, row_bits, T, ri, hold_to, plan, c);
+    if (b0 < ent0 && b0 + BLOCK * KPT > n_miss) {  // the planned batch's hits
+        int32_t v[KPT];
+#pragma unroll
+        for (int r = 0; r < KPT; ++r) {
+            const int64_t j = b0 + r * BLOCK + threadIdx.x - n_miss;
+            const bool in = j >= 0 && j < n_unique;
+            const int32_t h = in ? tk.hit[j] : 0, x = in ? tk.slot_u[j] : -1;
+            v[r] = h ? x : -1;  // a miss's entry may be written by its fill meanwhile
+        }
+#pragma unroll
+        for (int r = 0; r < KPT; ++r)
+            if ((uint32_t)v[r] < (uint64_t)nslots) {
+                last_use[v[r]] = u;
+                if (uses) uses[v[r]] += 1;  // one thread per unique key, so one per slot
+            }
+    }
+    for (int r = 0; r < KPT && b0 + r * BLOCK < n_miss; ++r) {
+        const int64_t t = b0 + r * BLOCK + threadIdx.x;
+        if (t < n_miss) {
+            if (commit_fill(t, map, tk, ri, row_bits, T, n_unique, nslots, key_of_slot, last_use,
+                            uses, u, prefetch, err)) {
+                const uint32_t key = tk.m_key[t];
+                const int32_t v = tk.v_slot[t];
+                const int tt = (int)(key >> row_bits);
+                int32_t q = 0;  // the last window batch with the key
+                if (wk.fast) {
+                    const int64_t row = ri.rbase[tt] + (key & ((1u << row_bits) - 1u));
+                    const int32_t lq = ri.lastq[row], pd = ri.pend[row];
+                    if (lq > plan + wk.n - 1) {  // from a window since shortened
+                        q = last_batch_with(wk, key);
+                    } else {
+                        q = lq >= plan ? lq - plan : 0;
+                        if (pd == wk.stamp && wk.ent > q) q = wk.ent;
+                    }
                 } else {
-                    q = lq >= plan ? lq - plan : 0;
-                    if (pd == wk.stamp && wk.ent > q) q = wk.ent;
+                    q = last_batch_with(wk, key);
                 }
-            } else {
-                q = last_batch_with(wk, key);
+                const int32_t off = q + wk.hold_past;
+                hold_to[v] = plan + off;
+                if (off < HOLD_SPAN) atomicAdd(&c[tt * HOLD_SPAN + off], 1);
             }
-            const int32_t off = q + wk.hold_past;
-            hold_to[v] = plan + off;
-            if (tt < T && off < HOLD_SPAN) atomicAdd(&c[tt * HOLD_SPAN + off], 1);
-        }
-    } else if (t >= ent0) {
-        if (t - ent0 < hr.start[hr.n])
-            hold_key(hold_ref(hr, t - ent0), row_bits, T, ri, hold_to, plan, c);
-    } else {
-        const int64_t j = t - n_miss;
-        if (j < n_unique && tk.hit[j]) {
-            const int32_t v = tk.slot_u[j];
-            if ((uint32_t)v < (uint64_t)nslots) {
-                last_use[v] = u;
-                if (uses) uses[v] += 1;  // one thread per unique key, so one per slot
-            }
-        }
-        if (j < nnz) {
-            const int32_t i = inv[j];
-            if ((uint32_t)i >= (uint64_t)n_unique) tk.slot_of[j] = -1;
-            else if (tk.hit[i]) tk.slot_of[j] = tk.slot_u[i];
         }
     }
     if (fills) {
@@ -828,23 +980,28 @@ __global__ void __launch_bounds__(BLOCK) k_commit(uint64_t *hash, uint32_t mask,
     }
 }
 
-void launch_commit(const Tables &tb, uint64_t *hash, uint32_t mask, TicketDev tk,
-                   const BatchDev &b, int64_t n_miss, int64_t n_unique, int64_t nnz,
-                   int32_t *key_of_slot, int32_t *last_use, int32_t *uses, int32_t u,
-                   bool prefetch, const WindowKeys &wk, const HoldRows &hr, const RowIndex &ri,
-                   int32_t *hold_to, int32_t *hcnt, DevCounters *cnt, hipStream_t s)
+void launch_commit(const Tables &tb, const HitMap &map, TicketDev tk, int64_t n_miss,
+                   int64_t n_unique, int32_t *key_of_slot, int32_t *last_use, int32_t *uses,
+                   int32_t u, bool prefetch, const WindowKeys &wk, const HoldRows &hr,
+                   const RowIndex &ri, int32_t *hold_to, int32_t *hcnt, DevCounters *cnt,
+                   hipStream_t s)
 {
-    // threads: misses, then the planned batch's keys and positions, then the
-    // entering batches' keys
-    const int64_t ent0 = n_miss + (nnz > n_unique ? nnz : n_unique);
+    // items: misses, then the planned batch's keys, then the entering
+    // batches' keys
+    const int64_t ent0 = n_miss + n_unique;
     const int64_t n = ent0 + (hr.n > 0 ? hr.start[hr.n] : 0);
     if (n <= 0) return;
     const int64_t nslots = tb.slot_base[tb.T];
-    hipLaunchKernelGGL(k_commit, dim3((unsigned)((n + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s,
-                       hash, mask, tk, (const int32_t *)b.inv, (const int32_t *)b.seg_off,
-                       (const uint32_t *)b.perm, n_miss, n_unique, nnz, nslots, key_of_slot,
-                       last_use, uses, u, (int32_t)prefetch, wk, hr, ri, ent0, tb.row_bits, tb.T,
-                       hold_to, hcnt, u, &cnt->err_sticky);
+    const int kpt = n >= COMMIT_FOUR ? 4 : 1;
+    const dim3 grid((unsigned)((n + BLOCK * kpt - 1) / (BLOCK * kpt)));
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, s, map, tk, n_miss, n_unique, nslots,
+                           key_of_slot, last_use, uses, u, (int32_t)prefetch, wk, hr, ri, ent0,
+                           tb.row_bits, tb.T, hold_to, hcnt, u, &cnt->err_sticky);
+    };
+    if (hr.n > 1) launch(kpt > 1 ? k_commit<4, false> : k_commit<1, false>);
+    else if (kpt > 1) launch(k_commit<4, true>);
+    else launch(k_commit<1, true>);
 }
 
 // ---------------------------------------------------------------- prefetch arrangement

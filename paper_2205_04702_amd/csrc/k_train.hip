@@ -53,20 +53,23 @@ __device__ __forceinline__ float4 reduce_rows(float4 acc)
     return acc;
 }
 
-// Sum of the rows src[idx[k]] for k in [beg, end), one wave, idx read 64 at a
-// time (coalesced) and broadcast by shuffles; each lane group takes every
+// Sum of the rows src[slot_u[inv[k]]] for k in [beg, end), one wave: inv read
+// 64 at a time (coalesced), the slots gathered (one table's few unique keys,
+// which stay in L2) and broadcast by shuffles; each lane group takes every
 // RPP-th row in order and UNROLL rows are in flight per lane.
 template <int LPR, int UNROLL>
 __device__ __forceinline__ float4 gather_sum(const float4 *__restrict__ src, int64_t nrows,
-                                             const int32_t *__restrict__ idx, int64_t beg,
-                                             int64_t end)
+                                             const int32_t *__restrict__ inv,
+                                             const int32_t *__restrict__ slot_u, int64_t n_unique,
+                                             int64_t beg, int64_t end)
 {
     constexpr int RPP = WAVE / LPR;
     const int lane = lane_id(), sub = lane / LPR, c = lane % LPR;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int64_t base = beg; base < end; base += WAVE) {
         const int n = (int)((end - base) < WAVE ? (end - base) : WAVE);
-        const int32_t my = lane < n ? idx[base + lane] : 0;
+        const int32_t ui = lane < n ? inv[base + lane] : 0;
+        const int32_t my = slot_u[(uint32_t)ui < (uint64_t)n_unique ? ui : 0];
         for (int k0 = 0; k0 < n; k0 += RPP * UNROLL) {
             float4 v[UNROLL];
 #pragma unroll
@@ -85,11 +88,16 @@ __device__ __forceinline__ float4 gather_sum(const float4 *__restrict__ src, int
 
 // ---------------------------------------------------------------- forward
 
-// out[g] = sum of Storage[slot_of[j]] over the positions j of bag g
+// out[g] = sum of Storage[slot_u[inv[j]]] over the positions j of bag g
 // (Sec. II-B, gather then element-wise reduction per table).  One wave per bag.
+// Reading each position's slot through its unique key costs a wave one more
+// round trip per 64 positions, hidden behind the other waves, and spares the
+// plan a pass that writes a slot per position (it was most of a large commit).
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ storage,
-                                                   const int32_t *__restrict__ slot_of,
+                                                   const int32_t *__restrict__ inv,
+                                                   const int32_t *__restrict__ slot_u,
+                                                   int64_t n_unique,
                                                    const int32_t *__restrict__ bag_off,
                                                    int64_t nbags, int64_t nslots,
                                                    float4 *__restrict__ out)
@@ -99,7 +107,8 @@ __global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ st
     if (g >= nbags) return;
     // at least 8 rows in flight per wave (a wave covers 64/LPR rows per load)
     constexpr int UNROLL = LPR >= 32 ? 8 : 4;
-    float4 acc = gather_sum<LPR, UNROLL>(storage, nslots, slot_of, bag_off[g], bag_off[g + 1]);
+    float4 acc = gather_sum<LPR, UNROLL>(storage, nslots, inv, slot_u, n_unique, bag_off[g],
+                                         bag_off[g + 1]);
     acc = reduce_rows<LPR>(acc);
     const int lane = lane_id();
     if (lane < LPR) out[g * LPR + lane] = acc;
@@ -219,10 +228,34 @@ __global__ void __launch_bounds__(BLOCK) k_backward(float4 *__restrict__ storage
     }
 }
 
-// Runs longer than one chunk (listed in `multi`, any order), one block per
-// run: the block's G lane groups add the run's chunk partials in a fixed
-// strided order (group g takes chunks g, g+G, ...), four loads in flight per
-// lane; group 0 then adds the G group sums in order and updates the row.
+// Runs longer than one chunk (listed in `multi`, any order): adds a run's chunk
+// partials in a fixed strided order (group g of the lane groups that work on
+// it takes chunks g, g + groups, ...; then the groups' sums in order) and
+// updates the row.  One wave takes a run; the few runs above COMBINE_WAVE
+// chunks (a hot row of a small table has thousands) are left to the whole
+// block, with eight partials in flight per lane, since the longest one ends
+// the launch.  With one block per run 21M IDs over 64 tables took 0.19 ms
+// alone, nearly all blocks adding a few partials with most lanes idle;
+// COMBINE_MS now.
+constexpr int COMBINE_WAVE = 64;
+
+template <int LPR, int UNROLL>
+__device__ __forceinline__ float4 sum_partials(const float4 *__restrict__ p, int64_t nch,
+                                               int64_t g, int64_t groups)
+{
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    int64_t q = g;
+    for (; q + (UNROLL - 1) * groups < nch; q += UNROLL * groups) {
+        float4 v[UNROLL];
+#pragma unroll
+        for (int k = 0; k < UNROLL; ++k) v[k] = p[(q + k * groups) * LPR];
+#pragma unroll
+        for (int k = 0; k < UNROLL; ++k) acc = f4_add(acc, v[k]);
+    }
+    for (; q < nch; q += groups) acc = f4_add(acc, p[q * LPR]);
+    return acc;
+}
+
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ storage,
                                                        const int32_t *__restrict__ multi,
@@ -232,33 +265,46 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
                                                        const float4 *__restrict__ partial,
                                                        int64_t nslots, float lr)
 {
-    constexpr int G = BLOCK / LPR;
+    constexpr int WAVES = BLOCK / WAVE, G = BLOCK / LPR;
     __shared__ float4 red[G][LPR];
-    const int64_t m = blockIdx.x;
-    if (m >= n_multi) return;  // uniform per block
-    const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
-    const int32_t s = multi[m];
-    const int64_t c0 = seg_chunk0[s];
-    const int64_t nch = seg_chunk0[s + 1] - c0;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    int64_t q = g;
-    for (; q + 3 * G < nch; q += 4 * G) {
-        float4 v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = partial[(c0 + q + k * G) * LPR + c];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc = f4_add(acc, v[k]);
+    __shared__ int32_t left[WAVES];  // each wave's run, if the block is to add it
+    const int w = wave_id(), lane = lane_id();
+    const int64_t m = (int64_t)blockIdx.x * WAVES + w;
+    const int32_t s = m < n_multi ? multi[m] : -1;
+    int64_t c0 = 0, nch = 0;
+    if (s >= 0) {
+        c0 = seg_chunk0[s];
+        nch = seg_chunk0[s + 1] - c0;
     }
-    for (; q < nch; q += G) acc = f4_add(acc, partial[(c0 + q) * LPR + c]);
-    red[g][c] = acc;
+    if (lane == 0) left[w] = nch > COMBINE_WAVE ? s : -1;
+    if (nch > 0 && nch <= COMBINE_WAVE) {  // uniform over the wave
+        const int c = lane % LPR;
+        const int32_t slot = slot_u[s];
+        const bool ok = (uint32_t)slot < (uint64_t)nslots;
+        float4 *const row = storage + (ok ? (int64_t)slot * LPR : 0) + c;
+        const float4 x = nt_load(row);
+        float4 acc = sum_partials<LPR, 4>(partial + c0 * LPR + c, nch, lane / LPR, WAVE / LPR);
+        acc = reduce_rows<LPR>(acc);
+        if (ok && lane < LPR) nt_store(row, sgd_step(x, acc, lr));
+    }
     __syncthreads();
-    if (g != 0) return;
-    float4 sum = red[0][c];
-    for (int k = 1; k < G; ++k) sum = f4_add(sum, red[k][c]);
-    const int32_t slot = slot_u[s];
-    if ((uint32_t)slot < (uint64_t)nslots) {
-        float4 *const w = storage + (int64_t)slot * LPR + c;
-        nt_store(w, sgd_step(nt_load(w), sum, lr));
+    for (int k = 0; k < WAVES; ++k) {
+        const int32_t run = left[k];
+        if (run < 0) continue;  // uniform over the block
+        const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
+        const int64_t b0 = seg_chunk0[run], n = seg_chunk0[run + 1] - b0;
+        red[g][c] = sum_partials<LPR, 8>(partial + b0 * LPR + c, n, g, G);
+        __syncthreads();
+        if (g == 0) {
+            float4 sum = red[0][c];
+            for (int q = 1; q < G; ++q) sum = f4_add(sum, red[q][c]);
+            const int32_t slot = slot_u[run];
+            if ((uint32_t)slot < (uint64_t)nslots) {
+                float4 *const row = storage + (int64_t)slot * LPR + c;
+                nt_store(row, sgd_step(nt_load(row), sum, lr));
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -425,13 +471,13 @@ void launch_move(float *storage, int dim, const Tables &tb, float *const *host_d
     default: hipExtLaunchKernelGGL(KERNEL<64>, GRID, dim3(BLOCK), 0, s, E0, E1, 0, __VA_ARGS__); break; \
     }
 
-void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *slot_of,
-                    const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
+void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *inv,
+                    const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
                     hipEvent_t e0, hipEvent_t e1)
 {
     if (nbags <= 0) return;
     SP_DISPATCH_LPR_EV(dim / 4, k_forward, grid_waves(nbags), e0, e1, (const float4 *)storage,
-                       slot_of, bag_off, nbags, nslots, (float4 *)out);
+                       inv, slot_u, n_unique, bag_off, nbags, nslots, (float4 *)out);
 }
 
 void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,
@@ -448,7 +494,7 @@ void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,
                        (const int4 *)b.chunk_desc, (const int32_t *)b.sbag, slot_u, n_chunks,
                        (const float4 *)grad, nbags, nslots, lr, (float4 *)partial);
     if (n_multi > 0)
-        SP_DISPATCH_LPR_EV(D4, k_bwd_combine, dim3((unsigned)n_multi), ev[2], ev[3],
+        SP_DISPATCH_LPR_EV(D4, k_bwd_combine, grid_waves(n_multi), ev[2], ev[3],
                            (float4 *)storage, (const int32_t *)b.multi, n_multi,
                            (const int32_t *)b.seg_chunk0, slot_u,
                            (const float4 *)partial, nslots, lr);

@@ -396,6 +396,14 @@ __device__ __forceinline__ int32_t hash_find_ro(const uint64_t *__restrict__ tab
     return -1;
 }
 
+// The slot of a row, or -1; nothing modifies the map meanwhile.  row: its
+// RowIndex place.
+__device__ __forceinline__ int32_t map_find_ro(const HitMap &m, uint32_t key, int64_t row)
+{
+    if (m.dense) return m.dense[row];  // uniform over the launch
+    return hash_find_ro(m.hash, m.mask, key);
+}
+
 // Marks key's entry erased.  Returns false if the key was absent.
 __device__ __forceinline__ bool hash_erase(uint64_t *tab, uint32_t mask, uint32_t key)
 {

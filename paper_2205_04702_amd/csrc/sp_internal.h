@@ -9,7 +9,7 @@ namespace sp {
 constexpr int MAX_TABLES = 64;
 constexpr int MAX_PF = 4;        // successor batches a plan may prefetch
 constexpr int MAX_WINDOW = 16;   // batches one plan may look at (lookahead <= 15)
-constexpr int QUERY_TILE = 256;  // unique keys per block of the query (one per thread)
+constexpr int QUERY_TILE = 256;  // unique keys per block of the query at least (one per thread)
 constexpr int SEL_BITS = 11;     // digit width of the LRU radix select
 constexpr int SEL_BINS = 1 << SEL_BITS;
 
@@ -68,7 +68,7 @@ struct DevCounters {
     int32_t pad2[3];
 };
 constexpr int COUNTERS_CLEARED = (int)(offsetof(DevCounters, err_sticky) / sizeof(int32_t));
-constexpr int PART_COPIES = 64;  // copies of the per-table counters the probe adds into
+constexpr int PART_COPIES = 16;  // copies of the per-table counters the probe adds into, at most
 // one copy: miss, held and the prefetch counts of each successor
 constexpr int PART_WORDS = (2 + MAX_PF) * MAX_TABLES;
 constexpr int COUNTER_WORDS = (int)(sizeof(DevCounters) / sizeof(int32_t));
@@ -94,11 +94,9 @@ inline int ingest_splits(int T) { return T <= 16 ? 16 : (T <= 32 ? 8 : 4); }
 // One window-ring entry: a batch as it arrived plus its sort/dedup products.
 struct BatchDev {
     int32_t *ids, *bag_off, *bag_of;  // raw CSR, bag of each position
-    uint32_t *perm;                  // position of each sorted key
     int32_t *sbag;                   // bag of each sorted position
     uint32_t *ukeys;                 // unique keys ascending
     int32_t *inv;                    // [nnz] index of each position's key in ukeys
-    int32_t *seg_off;                // [n_unique+1] start of each key's run of sorted positions
     int32_t *seg_chunk0;             // [n_unique+1] first backward chunk of each run
     int4 *chunk_desc;                // [n_chunks] first pos, end pos, run, above 1 when the run
                                      // has more chunks
@@ -111,11 +109,24 @@ struct BatchDev {
 // Per-plan device buffers.
 struct TicketDev {
     int32_t *hit, *slot_u;           // [n_unique]
-    int32_t *slot_of;                // [nnz]
     uint32_t *m_key;                 // [n_miss] missing keys ascending
     int32_t *m_uidx;                 // [n_miss] their index in ukeys
     int32_t *v_slot;                 // [n_miss] slot given to each miss
     int32_t *v_old_key, *v_old_lu;   // [n_miss] previous occupant / last use of that slot
+};
+
+// The Hit-Map (Sec. IV-D): which slot holds a row.  Where an entry per table
+// row takes no more memory than the hash would, it is `dense`, indexed as
+// RowIndex (-1: not cached); else the open-addressing hash of `mask` + 1
+// entries.  A batch's unique keys ascend, so its dense lookups walk the array
+// forwards, four bytes each, where every hash probe is a random 64-byte line,
+// and placing or erasing a row is one store instead of a probe chain with an
+// atomic; the hash keeps the memory in proportion to the slots when the tables
+// are far larger.
+struct HitMap {
+    uint64_t *hash;
+    uint32_t mask;
+    int32_t *dense;
 };
 
 // Replacement policies (Sec. VI-E): the values of SP_POLICY_*.
@@ -160,8 +171,10 @@ struct QueryRows {
     int32_t qoff[MAX_WINDOW];        // per probe-array index: its batch less the planned one
     uint32_t entrant;                // bit per probe-array index
     int32_t rebuild;
+    uint32_t known;                  // bit per probe-array index: eslot holds the batch's slots
+                                     // as of its entry (a row cached then is held since)
     int32_t span;                    // lookahead + hold_past
-    int32_t *eslot[MAX_WINDOW];      // per probe-array index: where an entrant's slots go
+    int32_t *eslot[MAX_WINDOW];      // per probe-array index: where an entrant's slots go (known: are)
 };
 
 // The batches entering the hold window, as their slots are marked held:
@@ -286,7 +299,7 @@ struct PrefetchDev {
     int32_t *flag;
     int64_t stride;
 };
-void launch_query(const Tables &tb, const uint64_t *hash, uint32_t mask,
+void launch_query(const Tables &tb, const HitMap &map,
                   const uint32_t *const *ukeys, const int32_t *const *nuniq, int nwin,
                   int64_t max_unique, const int32_t *hold_to, int32_t *held, int32_t stamp,
                   int32_t *hcnt, int32_t plan, const QueryRows &qr, const RowIndex &ri,
@@ -321,14 +334,13 @@ struct WindowKeys {
     const int32_t *nu[MAX_WINDOW];
 };
 // Misses into their victim slots, Hit-Map and slot metadata updated, every
-// slot the batch uses touched (last_use = u), slot_of filled.  A filled row is
+// slot the batch uses touched (last_use = u), slot_u completed.  A filled row is
 // held through the last window batch that has its key (plus hold_past), and
 // the cached keys of the entering batches hr (none after a rebuild) are
 // marked held.
 // uses: per-slot use counts (LFU), or null when the policy does not keep them
-void launch_commit(const Tables &tb, uint64_t *hash, uint32_t mask, TicketDev tk,
-                   const BatchDev &b, int64_t n_miss, int64_t n_unique, int64_t nnz,
-                   int32_t *key_of_slot, int32_t *last_use, int32_t *uses, int32_t u,
+void launch_commit(const Tables &tb, const HitMap &map, TicketDev tk, int64_t n_miss,
+                   int64_t n_unique, int32_t *key_of_slot, int32_t *last_use, int32_t *uses, int32_t u,
                    bool prefetch, const WindowKeys &wk, const HoldRows &hr, const RowIndex &ri,
                    int32_t *hold_to, int32_t *hcnt, DevCounters *cnt, hipStream_t s);
 // Prefetch mode: the ticket's miss list, per table the planned batch's own
@@ -348,8 +360,8 @@ void launch_pf_arrange(const Tables &tb, PrefetchDev pf, int64_t n_own,
 // staged fill), else straight from the mapped host table.
 void launch_move(float *storage, int dim, const Tables &tb, float *const *host_dev, TicketDev tk,
                  int64_t n_miss, int32_t u, float *stage, const float *staged, hipStream_t s);
-void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *slot_of,
-                    const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
+void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *inv,
+                    const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
                     hipEvent_t e0, hipEvent_t e1);
 // The fixed partial-sum array of sp_backward_update_static: its bytes, and
 // its device address on the current device.
