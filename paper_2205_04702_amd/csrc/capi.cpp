@@ -145,6 +145,7 @@ struct TicketHost {
     bool keys_direct = false;  // the query wrote the missing keys to pinned host memory
     int64_t nnz = 0, n_unique = 0, n_chunks = 0, n_multi = 0, n_miss = 0;
     int64_t n_own = 0;  // misses of the planned batch itself (n_miss less prefetched rows)
+    int64_t prior_fill = -1;  // mapped fill: the last earlier plan with misses
     bool ev_planned = false;  // the plan recorded ev_planned (event-wait mode at plan time)
     int32_t B = 0;
     int ring = 0;
@@ -207,7 +208,13 @@ class Pool {
             work_ = &w;
             ++gen_;
         }
-        cv_start_.notify_all();
+        // no more helpers than pieces left for them: waking one costs the
+        // caller a few microseconds
+        const int64_t pieces = (n + grain - 1) / grain - 1;
+        if (pieces < (int64_t)threads_.size())
+            for (int64_t i = 0; i < pieces; ++i) cv_start_.notify_one();
+        else
+            cv_start_.notify_all();
         take(w);
         std::unique_lock<std::mutex> lk(m_);
         work_ = nullptr;  // helpers that have not joined yet stay out
@@ -331,6 +338,11 @@ constexpr int SEM_PLANNED = 0, SEM_FILLED = 8, SEM_WORDS = 16;
 constexpr int SEM_UPD = SEM_WORDS;
 static int sem_words(int nring) { return SEM_UPD + 8 * nring; }
 
+// A host batch's arrays in its ring entry: the offsets, then the IDs from
+// here on.
+constexpr int64_t ID_ALIGN = 64;
+static int64_t ids_at(int64_t nbags) { return (nbags + ID_ALIGN) / ID_ALIGN * ID_ALIGN; }
+
 // staging slots of evicted rows (fill of plan p, copy of plan p - 1 and the
 // host scatter of plan p - 2 can all be in flight)
 constexpr int MAX_NSTAGE = 3;
@@ -347,6 +359,10 @@ constexpr int64_t FILL_ITEM_BYTES = 1ll << 20;
 // threads (one reaches a fraction of the host's memory bandwidth).
 constexpr int64_t IDCOPY_ABOVE_BYTES = 8ll << 20;
 constexpr int64_t IDCOPY_GRAIN_BYTES = 2ll << 20;
+// rows per piece of the write-back scatter: at least this many bytes (a thread
+// writes them in about 10 us; 1.7k rows of 128 bytes took 13 us on two threads,
+// 27 us with eight woken for four pieces, and the step 71 and 79 us)
+constexpr int64_t SCATTER_PIECE_BYTES = 64 << 10;
 // write-back copies above this size go on the ingest stream, where they
 // overlap the next fill; smaller ones go on the copy stream
 constexpr int64_t SMALL_COPY_BYTES = 8ll << 20;
@@ -461,6 +477,14 @@ struct sp_ctx {
     // previous keys.  Plan p's copy to the host is issued by plan p + 1 (or by
     // flush), when its fill has nearly always finished: copy_pending = p
     float *stage_dev[MAX_NSTAGE]{}, *stage_host[MAX_NSTAGE]{};
+    // mapped fill: the move kernel writes the evicted rows straight to the
+    // pinned staging (stage_dev is its device-visible address), slot
+    // fills % nstage; slot_ticket: the last plan whose rows are in the slot
+    int64_t fills = 0;
+    int64_t slot_ticket[MAX_NSTAGE]{-1, -1, -1};
+    int64_t last_job = -1;     // last plan handed to the write-back thread
+    int64_t last_fill = -1;    // mapped fill: last plan with misses
+    int64_t filled_upto = -1;  // mapped fill: fills of plans up to this one are known done
     hipEvent_t ev_d2h[MAX_NSTAGE]{};
     int nstage = 3;  // staging slots in use
     int64_t copy_pending = -1, copy_n = 0;
@@ -514,9 +538,10 @@ struct sp_ctx {
     bool poison = false;
 
     // pinned copies of window arrays handed over in host memory, per ring
-    // entry: the caller's arrays are copied here on the host, then to the
-    // device asynchronously (ev_ids: that copy has run)
-    std::vector<int32_t *> h_ids, h_off;
+    // entry: the caller's arrays are copied here on the host (the offsets,
+    // then from ids_at on the IDs), then to the device asynchronously in one
+    // copy (ev_ids: that copy has run)
+    std::vector<int32_t *> h_off;
     std::vector<hipEvent_t> ev_ids;
     std::vector<char> ids_pending;
 
@@ -603,7 +628,7 @@ static sp_status palloc(sp_ctx *h, T **p, int64_t count)
         *p = nullptr;
         return fail(h, SP_ERR_OOM, "hipHostMalloc(%zu) failed: injected (SP_FAIL_ALLOC_AFTER)", bytes);
     }
-    hipError_t e = hipHostMalloc((void **)p, bytes, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void **)p, bytes, hipHostMallocMapped);
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -642,7 +667,9 @@ static void worker_main(sp_ctx *h)
                 h->worker_err = e;
             } else {
                 std::atomic<int64_t> wr{0};
-                h->scatter.run(j.n, 512, [&](int64_t b, int64_t e2) {
+                // pieces that are worth waking a thread for
+                const int64_t grain = std::max<int64_t>(512, SCATTER_PIECE_BYTES / (int64_t)row_bytes);
+                h->scatter.run(j.n, grain, [&](int64_t b, int64_t e2) {
                     wr += copy_rows(h->host, h->tb, h->D, const_cast<float *>(j.rows), j.keys,
                                     b, e2, true);
                 });
@@ -972,8 +999,7 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     h->upd_val.assign(h->nring, 0);
     for (int r = 0; r < h->nring; ++r) {
         BatchDev &b = h->ring[r];
-        TRY(dalloc(h, &b.ids, N));
-        TRY(dalloc(h, &b.bag_off, TB1));
+        TRY(dalloc(h, &b.bag_off, TB1 + ID_ALIGN + N));  // and, for host batches, the IDs behind
         TRY(dalloc(h, &b.bag_of, N));
         TRY(dalloc(h, &b.sbag, N));
         TRY(dalloc(h, &b.ukeys, N));
@@ -985,13 +1011,11 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         TRY(dalloc(h, &b.scal, T + 3));
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ring_ready[r], hipEventDisableTiming));
     }
-    h->h_ids.assign(h->nring, nullptr);
     h->h_off.assign(h->nring, nullptr);
     h->ev_ids.assign(h->nring, nullptr);
     h->ids_pending.assign(h->nring, 0);
     for (int r = 0; r < h->nring; ++r) {
-        TRY(palloc(h, &h->h_ids[r], N));
-        TRY(palloc(h, &h->h_off[r], TB1));
+        TRY(palloc(h, &h->h_off[r], TB1 + ID_ALIGN + N));
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ev_ids[r], hipEventDisableTiming));
     }
     for (int k = 0; k < h->nring; ++k) {
@@ -1050,8 +1074,9 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     h->stage_rows = std::min<int64_t>(NM, S);
     h->nstage = MAX_NSTAGE;
     for (int i = 0; i < h->nstage; ++i) {
-        TRY(dalloc(h, &h->stage_dev[i], h->stage_rows * (h->D + 1)));
         TRY(palloc(h, &h->stage_host[i], h->stage_rows * (h->D + 1)));
+        if (h->staged) TRY(dalloc(h, &h->stage_dev[i], h->stage_rows * (h->D + 1)));
+        else HIPCHK(nullptr, hipHostGetDevicePointer((void **)&h->stage_dev[i], h->stage_host[i], 0));
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ev_d2h[i], hipEventDisableTiming));
         if (h->staged) {  // at most min(misses, slots) rows per plan, like the write-back
             {  // device-mapped: the query writes the missing keys here itself
@@ -1308,19 +1333,17 @@ static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead,
         // (the caller's arrays are free again right after), then to the ring
         // asynchronously.  The buffers' previous copy (batch q - nring, or
         // this batch before a rejected plan) has long run.
+        const int64_t at = ids_at(nbags);
         if (!prestaged) {
             if (h->ids_pending[r]) HIPCHK(h, hipEventSynchronize(h->ev_ids[r]));
-            copy_host(h, h->h_ids[r], bt.ids, (int64_t)sizeof(int32_t) * bt.nnz);
+            copy_host(h, h->h_off[r] + at, bt.ids, (int64_t)sizeof(int32_t) * bt.nnz);
             memcpy(h->h_off[r], bt.bag_off, sizeof(int32_t) * (nbags + 1));
         }
-        if (bt.nnz > 0)
-            HIPCHK(h, hipMemcpyAsync(b.ids, h->h_ids[r], sizeof(int32_t) * bt.nnz,
-                                     hipMemcpyHostToDevice, si));
-        HIPCHK(h, hipMemcpyAsync(b.bag_off, h->h_off[r], sizeof(int32_t) * (nbags + 1),
+        HIPCHK(h, hipMemcpyAsync(b.bag_off, h->h_off[r], sizeof(int32_t) * (at + bt.nnz),
                                  hipMemcpyHostToDevice, si));
         HIPCHK(h, hipEventRecord(h->ev_ids[r], si));
         h->ids_pending[r] = 1;
-        ids = b.ids;
+        ids = b.bag_off + at;
         off = b.bag_off;
     }
     IngestCons ic{h->cons_counter, 0, h->h_cnt_dev + COUNTER_WORDS, 0};
@@ -1352,7 +1375,17 @@ static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead,
     return SP_OK;
 }
 
-// Issue the pending write-back copy (plan p = copy_pending) on stream s and
+static void push_job(sp_ctx *h, const Job &job)
+{
+    {
+        std::lock_guard<std::mutex> lk(h->mu);
+        h->jobs.push_back(job);
+    }
+    h->cv.notify_one();
+    h->last_job = job.ticket;
+}
+
+// Staged fill: issue the pending write-back copy (plan p = copy_pending) on stream s and
 // hand its rows to the write-back thread.  The host staging slot was last
 // used by plan p - nstage, whose scatter is joined first.
 static sp_status issue_copy(sp_ctx *h, hipStream_t s)
@@ -1385,11 +1418,7 @@ static sp_status issue_copy(sp_ctx *h, hipStream_t s)
         job.keys = (const int32_t *)(h->stage_host[sl] + n * h->D);
         job.n = n;
     }
-    {
-        std::lock_guard<std::mutex> lk(h->mu);
-        h->jobs.push_back(job);
-    }
-    h->cv.notify_one();
+    push_job(h, job);
     h->copy_pending = -1;
     return SP_OK;
 }
@@ -1421,9 +1450,9 @@ static sp_status defer_ahead(sp_ctx *h, const sp_batch *window, int n, int from,
         if (!bt.on_device) {
             if (h->ids_pending[r]) HIPCHK(h, hipEventSynchronize(h->ev_ids[r]));
             h->ids_pending[r] = 0;
-            copy_host(h, h->h_ids[r], bt.ids, (int64_t)sizeof(int32_t) * bt.nnz);
-            memcpy(h->h_off[r], bt.bag_off,
-                   sizeof(int32_t) * ((int64_t)h->T * bt.batch + 1));
+            const int64_t nbags = (int64_t)h->T * bt.batch;
+            copy_host(h, h->h_off[r] + ids_at(nbags), bt.ids, (int64_t)sizeof(int32_t) * bt.nnz);
+            memcpy(h->h_off[r], bt.bag_off, sizeof(int32_t) * (nbags + 1));
         }
         h->deferred.push_back({bt, q});
     }
@@ -1602,6 +1631,95 @@ static sp_status enqueue_query(sp_ctx *h, int64_t k, int nhold, uint32_t *seq_ou
     if (host_keys) HIPCHK(h, hipEventRecord(h->ev_mkey[sl], h->s_plan));  // the keys are complete
     if (h->ws_plan.overflow) return fail(h, SP_ERR_HIP, "internal: scan workspace too small");
     if (timing) HIPCHK(h, h->t_qry.end(h->s_plan));
+    return SP_OK;
+}
+
+// The fill of plan k and the write-back of the rows it evicts, on the move
+// stream.
+static sp_status plan_fill(sp_ctx *h, int64_t k, int nhold, int pf_d, bool timing)
+{
+    const int e = (int)(k % h->nring);
+    const TicketHost &th = h->tkh[e];
+    if (!h->staged) TRY(join_writebacks(h, k));  // the staged fill joined before its gather
+    const int sl = (int)((h->staged ? k : h->fills) % h->nstage);
+    // mapped fill: the slot's last rows are in the host tables
+    if (!h->staged && h->slot_ticket[sl] >= 0) TRY(join_jobs(h, h->slot_ticket[sl]));
+    MoveJob mj;
+    mj.k = k;
+    mj.n = th.n_miss;
+    mj.sl = sl;
+    mj.e = e;
+    mj.u = (int32_t)k;
+    mj.timing = timing;
+    // the device staging slot is free once plan k - nstage's copy has run
+    // (issued two plans ago)
+    if (h->staged && k >= h->nstage && hipEventQuery(h->ev_d2h[sl]) != hipSuccess) {
+        (void)hipGetLastError();
+        mj.wait[mj.nwait++].ev = h->ev_d2h[sl];
+    }
+    if (th.ev_planned) {
+        mj.wait[mj.nwait++].ev = h->ev_planned[e];
+    } else {
+        Wait &w = mj.wait[mj.nwait++];
+        w.addr = h->sem + SEM_PLANNED;
+        w.val = (uint64_t)k + 1;
+    }
+    if (mj.n > 0) {
+        // RAW-2/3: a victim's row is final once the last update that used it
+        // has run.  Update j freed ring entry j % nring for batch j + nring,
+        // whose ingest waited for it; this plan's query is behind every batch
+        // up to k+L, so updates up to k+L-nring are behind this stream
+        // already.  Batches k-P .. k-1 of the past window cannot have used a
+        // victim's row (their rows are held), and the fill writes only victim
+        // slots, so their updates need no wait.  The rest are waited for, one
+        // wait when they share a stream.
+        // (a value wait: a wait on a pending event costs the host far more)
+        const int64_t last = k - 1 - h->P;
+        for (int64_t j = std::max<int64_t>(0, k + h->L + 1 - h->nring); j <= last; ++j) {
+            const int ej = (int)(j % h->nring);
+            if (j != last && h->upd_stream[ej] == h->upd_stream[last % h->nring]) continue;
+            if (hipEventQuery(h->ev_upd[ej]) == hipSuccess) continue;  // already done
+            (void)hipGetLastError();
+            if (mj.nwait == (int)(sizeof mj.wait / sizeof mj.wait[0]))
+                return fail(h, SP_ERR_HIP, "internal: too many waits for the fill");
+            Wait &w = mj.wait[mj.nwait++];
+            if (!h->upd_val[ej]) {  // that update wrote no word (event-wait mode then)
+                w.ev = h->ev_upd[ej];
+            } else {
+                w.addr = h->sem + SEM_UPD + 8 * ej;
+                w.val = (uint64_t)j + 1;
+            }
+        }
+    }
+    if (h->staged) {
+        {
+            std::lock_guard<std::mutex> lk(h->fmu);
+            h->fjobs.push_back(mj);
+        }
+        h->fcv.notify_one();
+        // a small one goes on the copy stream now: it ends long before the next
+        // fill, even where its queue is the move stream's
+        TRY(issue_copy(h, h->s_copy));
+        h->copy_pending = k;
+        h->copy_n = mj.n;
+    } else {
+        HIPCHK(h, enqueue_move(h, mj, nullptr));
+        h->last_fill = k;
+        if (h->last_fresh) return SP_OK;  // never-used slots: nothing to write back
+        Job job;
+        job.ticket = k;
+        job.ev = h->ev_filled[e];
+        job.rows = h->stage_host[sl];
+        job.keys = (const int32_t *)(h->stage_host[sl] + mj.n * h->D);
+        job.n = mj.n;
+        push_job(h, job);
+        h->slot_ticket[sl] = k;
+        ++h->fills;
+    }
+    // an evicted row is in no batch of this plan's window, so the first plan
+    // that can fill it again is the one whose planned batch (or, prefetching,
+    // next batch) is the first after the window
+    h->deadlines.emplace_back(k, k + nhold - pf_d);
     return SP_OK;
 }
 
@@ -1889,73 +2007,8 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     tF = tG;
     // ---- mover (own stream): write-back of evicted rows and fill of misses;
     // the next plan's query does not wait for it
-    if (!h->staged) TRY(join_writebacks(h, k));  // the staged fill joined before its gather
-    const int sl = (int)(k % h->nstage);
-    MoveJob mj;
-    mj.k = k;
-    mj.n = n_miss;
-    mj.sl = sl;
-    mj.e = e;
-    mj.u = u;
-    mj.timing = timing;
-    // the device staging slot is free once plan k - nstage's copy has run
-    // (issued two plans ago)
-    if (k >= h->nstage && hipEventQuery(h->ev_d2h[sl]) != hipSuccess) {
-        (void)hipGetLastError();
-        mj.wait[mj.nwait++].ev = h->ev_d2h[sl];
-    }
-    if (th.ev_planned) {
-        mj.wait[mj.nwait++].ev = h->ev_planned[e];
-    } else {
-        Wait &w = mj.wait[mj.nwait++];
-        w.addr = h->sem + SEM_PLANNED;
-        w.val = (uint64_t)k + 1;
-    }
-    if (n_miss > 0) {
-        // RAW-2/3: a victim's row is final once the last update that used it
-        // has run.  Update j freed ring entry j % nring for batch j + nring,
-        // whose ingest waited for it; this plan's query is behind every batch
-        // up to k+L, so updates up to k+L-nring are behind this stream
-        // already.  Batches k-P .. k-1 of the past window cannot have used a
-        // victim's row (their rows are held), and the fill writes only victim
-        // slots, so their updates need no wait.  The rest are waited for, one
-        // wait when they share a stream.
-        // (a value wait: a wait on a pending event costs the host far more)
-        const int64_t last = k - 1 - h->P;
-        for (int64_t j = std::max<int64_t>(0, k + h->L + 1 - h->nring); j <= last; ++j) {
-            const int ej = (int)(j % h->nring);
-            if (j != last && h->upd_stream[ej] == h->upd_stream[last % h->nring]) continue;
-            if (hipEventQuery(h->ev_upd[ej]) == hipSuccess) continue;  // already done
-            (void)hipGetLastError();
-            if (mj.nwait == (int)(sizeof mj.wait / sizeof mj.wait[0]))
-                return fail(h, SP_ERR_HIP, "internal: too many waits for the fill");
-            Wait &w = mj.wait[mj.nwait++];
-            if (!h->upd_val[ej]) {  // that update wrote no word (event-wait mode then)
-                w.ev = h->ev_upd[ej];
-            } else {
-                w.addr = h->sem + SEM_UPD + 8 * ej;
-                w.val = (uint64_t)j + 1;
-            }
-        }
-    }
-    if (h->staged) {
-        {
-            std::lock_guard<std::mutex> lk(h->fmu);
-            h->fjobs.push_back(mj);
-        }
-        h->fcv.notify_one();
-    } else {
-        HIPCHK(h, enqueue_move(h, mj, nullptr));
-    }
-    // a small one goes on the copy stream now: it ends long before the next
-    // fill, even where its queue is the move stream's
-    TRY(issue_copy(h, h->s_copy));
-    h->copy_pending = k;
-    h->copy_n = n_miss;
-    // an evicted row is in no batch of this plan's window, so the first plan
-    // that can fill it again is the one whose planned batch (or, prefetching,
-    // next batch) is the first after the window
-    h->deadlines.emplace_back(k, k + nhold - pf_d);
+    th.prior_fill = h->last_fill;
+    if (h->staged || n_miss > 0) TRY(plan_fill(h, k, nhold, pf_d, timing));
 
     h->host_ms[4] += host_ms() - tF;
     h->planned = k + 1;
@@ -2002,7 +2055,24 @@ extern "C" sp_status sp_forward(sp_handle h, int64_t ticket, float *d_out, void 
     const bool ev = h->flags & SP_FLAG_EVENT_WAITS;
     // staged fill: the fill waited for must be enqueued before anything waits on it
     TRY(join_fill(h, th.n_own > 0 || ticket == 0 ? ticket : ticket - 1));
-    if (th.n_own > 0 || ticket == 0) {
+    if (!h->staged && th.n_own == 0) {
+        // mapped fill: plans without misses enqueue none, so the fill to wait
+        // for is the last earlier one, if it is not known done
+        const int64_t f = th.prior_fill;
+        if (f > h->filled_upto) {
+            const hipError_t q = hipEventQuery(h->ev_filled[f % h->nring]);
+            if (q == hipSuccess) h->filled_upto = f;
+            else if (q != hipErrorNotReady) return fail(h, SP_ERR_HIP, "fill of plan %lld: %s", (long long)f, hipGetErrorString(q));
+        }
+        if (f > h->filled_upto) {
+            if (ev) HIPCHK(h, hipStreamWaitEvent(s, h->ev_filled[f % h->nring], 0));
+            else HIPCHK(h, hipStreamWaitValue64(s, h->sem + SEM_FILLED, (uint64_t)f + 1,
+                                                hipStreamWaitValueGte, ~0ull));
+        }
+        if (ev && th.ev_planned) HIPCHK(h, hipStreamWaitEvent(s, h->ev_planned[e], 0));
+        else HIPCHK(h, hipStreamWaitValue64(s, h->sem + SEM_PLANNED, (uint64_t)ticket + 1,
+                                            hipStreamWaitValueGte, ~0ull));
+    } else if (th.n_own > 0 || ticket == 0) {
         if (ev) HIPCHK(h, hipStreamWaitEvent(s, h->ev_filled[e], 0));
         else HIPCHK(h, hipStreamWaitValue64(s, h->sem + SEM_FILLED, (uint64_t)ticket + 1,
                                             hipStreamWaitValueGte, ~0ull));
@@ -2062,7 +2132,9 @@ static sp_status backward_update(sp_handle h, int64_t ticket, const float *d_gra
                     partial, s, ev);
     CHECK_LAUNCH(h);
     HIPCHK(h, hipEventRecord(h->ev_upd[e], s));  // also frees ring entry e of the window
-    h->upd_val[e] = !(h->flags & SP_FLAG_EVENT_WAITS);
+    // a plan without misses is mostly followed by others: a fill that has to
+    // wait for its update after all waits for the event
+    h->upd_val[e] = !(h->flags & SP_FLAG_EVENT_WAITS) && th.n_miss > 0;
     if (h->upd_val[e])  // for the value wait of a later fill
         HIPCHK(h, hipStreamWriteValue64(s, h->sem + SEM_UPD + 8 * e, (uint64_t)ticket + 1, 0));
     h->upd_stream[e] = s;
@@ -2099,7 +2171,7 @@ extern "C" sp_status sp_flush(sp_handle h)
     TRY(join_fill(h, h->planned - 1));
     TRY(issue_copy(h, h->s_copy));
     HIPCHK(h, hipDeviceSynchronize());
-    TRY(join_jobs(h, h->planned - 1));
+    TRY(join_jobs(h, h->last_job));
     h->deadlines.clear();
     std::vector<int32_t> keys((size_t)h->total_slots);
     HIPCHK(h, hipMemcpy(keys.data(), h->key_of_slot, sizeof(int32_t) * h->total_slots,
@@ -2130,7 +2202,7 @@ extern "C" sp_status sp_sync(sp_handle h)
     TRY(join_fill(h, h->planned - 1));
     TRY(issue_copy(h, h->s_copy));
     HIPCHK(h, hipDeviceSynchronize());
-    TRY(join_jobs(h, h->planned - 1));
+    TRY(join_jobs(h, h->last_job));
     h->deadlines.clear();  // every write-back has landed
     return SP_OK;
 }

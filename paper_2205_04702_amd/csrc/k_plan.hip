@@ -56,8 +56,8 @@ __device__ __forceinline__ P pick_uniform(const P (&a)[MAX_WINDOW], int w)
 // What bounds it: the chain of dependent accesses when small; when large,
 // random accesses and, before, device-scope atomics (one exchange per entering
 // key, three on one address per block of 256 keys): KPT keys per thread then
-// cut the blocks.  2.1M unique keys a batch: 2.24 ms before, QUERY_MS_MIXED
-// now; 1.05M: 0.58 ms before, QUERY_MS_26 now.
+// cut the blocks.  2.1M unique keys a batch: 2.24 ms before, 0.06 ms
+// now; 1.05M: 0.58 ms before, 0.04 ms now.
 //
 // Every add a block makes returns its old value, and each thread tests the
 // values before the block's barrier, so all of a block's adds have been
@@ -904,7 +904,7 @@ __device__ __forceinline__ int32_t last_batch_with(const WindowKeys &wk, uint32_
 // entering batch.  Bound by random 4-byte accesses (last_use of the hits,
 // hold_to of the entering keys) when large, by the chain of a fill when small.
 // 2.1M unique keys a batch: 1.03 ms while it also wrote a slot per position and
-// raised hold_to by atomics, COMMIT_MS now.
+// raised hold_to by atomics, 0.14 ms now.
 constexpr int64_t COMMIT_FOUR = 512 << 10;  // items from which a thread takes four
 template <int KPT, bool ONE>
 __global__ void __launch_bounds__(BLOCK) k_commit(HitMap map, TicketDev tk, int64_t n_miss,

@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(BLOCK) k_backward(float4 *__restrict__ storage
 // block, with eight partials in flight per lane, since the longest one ends
 // the launch.  With one block per run 21M IDs over 64 tables took 0.19 ms
 // alone, nearly all blocks adding a few partials with most lanes idle;
-// COMBINE_MS now.
+// 0.135 ms now.
 constexpr int COMBINE_WAVE = 64;
 
 template <int LPR, int UNROLL>
@@ -315,12 +315,21 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
 // from the pinned host table (zero-copy over the host link), or, with the
 // staged fill, from row i of the rows already copied to the device.  The same
 // lanes read the old row before writing the new one.  Every victim's previous
-// key is stored after the n staging rows, so rows and keys leave the device
-// in one copy.  For the zero-copy fill the grid is kept small and each lane
-// group keeps MOVE_ROWS victims in flight: waves waiting on the host link
-// then occupy few compute units, and the kernels running beside this one
-// keep the rest.  The staged fill only moves rows within HBM and takes a
-// full grid.
+// key is stored after the n staging rows.  With the zero-copy fill the staging
+// is pinned host memory too: the old rows cross the link in the other
+// direction while the missing ones are read, and the write-back needs no copy
+// of its own.  (Such a copy ran beside the forward that waits for this kernel
+// and held it: 8 tables of 1M rows of 64 floats, 10.4k misses a step: 55 us
+// here, then a forward of 50 us; now 82 and 6.)  With the staged fill it is
+// device memory, copied later: there the link is busy with the gathered rows.
+// For the zero-copy fill the grid is kept small and each lane
+// group keeps MOVE_ROWS victims in flight: some four thousand 64-byte reads
+// fill the link's latency, and more only queue up in front of every other
+// kernel's misses.  89k rows of 32 bytes: 0.30 ms with 4096 reads in flight
+// and the next plan's query beside it 0.026 ms; 0.27 ms with 32k reads, and
+// the query 0.26 ms (a step 0.40 and 0.48 ms).  10.4k rows of 256 bytes: 94 us
+// with 4096 reads of 64 bytes, 82 us with 8192 and 80 us with 16384.  The
+// staged fill only moves rows within HBM and takes a full grid.
 // Every row the move reads or writes is touched once, so none of its accesses
 // keeps the line in the caches: cached stores of a large fill left the caches
 // full of dirty lines, whose write-back then slowed the forward that follows
@@ -334,8 +343,11 @@ __device__ __forceinline__ void nt_row_store(float4 *p, nv4f x)
     __builtin_nontemporal_store(x, reinterpret_cast<nv4f *>(p));
 }
 
-constexpr int MOVE_MAX_BLOCKS = 64;
+constexpr int MOVE_MAX_BLOCKS = 32;
 constexpr int MOVE_ROWS = 4;
+// blocks of the zero-copy fill: a lane reads 16 bytes, and rows below 64 bytes
+// take a read each
+constexpr int move_blocks(int lpr) { return 4 * lpr < MOVE_MAX_BLOCKS ? 4 * lpr : MOVE_MAX_BLOCKS; }
 
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK) k_move(float4 *__restrict__ storage, Tables tb,
@@ -348,6 +360,10 @@ __global__ void __launch_bounds__(BLOCK) k_move(float4 *__restrict__ storage, Ta
     const int64_t g = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / LPR;
     const uint32_t row_mask = (1u << tb.row_bits) - 1u;
     int32_t *const old_keys = reinterpret_cast<int32_t *>(stage + n * LPR);
+    // whole lines at a time: the staging may be host memory
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * BLOCK)
+        old_keys[i] = tk.v_old_key[i];
     for (int64_t i0 = g; i0 < n; i0 += groups * MOVE_ROWS) {
         // Straight-line code over the pass's MOVE_ROWS victims, with no branch
         // around a load: an entry past n reads entry i0's indices, and one
@@ -401,7 +417,6 @@ __global__ void __launch_bounds__(BLOCK) k_move(float4 *__restrict__ storage, Ta
 #pragma unroll
         for (int q = 0; q < MOVE_ROWS; ++q) {
             const int64_t i = i0 + q * groups;
-            if (in[q] && c == 0) old_keys[i] = old[q];
             if (v[q] >= 0 && old[q] >= 0) nt_row_store(stage + i * LPR + c, prev[q]);
             if (src[q]) nt_row_store(storage + (int64_t)v[q] * LPR + c, next[q]);
         }
@@ -453,7 +468,7 @@ void launch_move(float *storage, int dim, const Tables &tb, float *const *host_d
     for (int t = 0; t < tb.T; ++t) hr.p[t] = (const float4 *)host_dev[t];
     // each lane group places MOVE_ROWS victims per pass
     dim3 grid = grid_rows((n_miss + MOVE_ROWS - 1) / MOVE_ROWS, D4);
-    if (!staged) grid.x = grid.x < (unsigned)MOVE_MAX_BLOCKS ? grid.x : (unsigned)MOVE_MAX_BLOCKS;
+    if (!staged) grid.x = grid.x < (unsigned)move_blocks(D4) ? grid.x : (unsigned)move_blocks(D4);
     SP_DISPATCH_LPR(D4, k_move, grid, (float4 *)storage, tb, hr, tk, n_miss,
                     tb.slot_base[tb.T], (float4 *)stage, (const float4 *)staged);
 }

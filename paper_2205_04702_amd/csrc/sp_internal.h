@@ -93,7 +93,7 @@ inline int ingest_splits(int T) { return T <= 16 ? 16 : (T <= 32 ? 8 : 4); }
 
 // One window-ring entry: a batch as it arrived plus its sort/dedup products.
 struct BatchDev {
-    int32_t *ids, *bag_off, *bag_of;  // raw CSR, bag of each position
+    int32_t *bag_off, *bag_of;       // bag offsets, bag of each position
     int32_t *sbag;                   // bag of each sorted position
     uint32_t *ukeys;                 // unique keys ascending
     int32_t *inv;                    // [nnz] index of each position's key in ukeys
