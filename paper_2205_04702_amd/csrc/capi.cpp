@@ -446,6 +446,7 @@ struct sp_ctx {
     SortWs ws_sort{};
     ScanWs ws_ingest;
     int32_t *sel_state = nullptr, *sel_hist = nullptr;
+    uint32_t *sel_key = nullptr;  // [total_slots] priorities, while victims are chosen
     uint32_t *vk0 = nullptr, *vv0 = nullptr, *vk1 = nullptr;
     float *partial = nullptr;
     float *static_partial = nullptr;  // this device's fixed array (sp_backward_update_static)
@@ -1070,6 +1071,7 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     }
     TRY(dalloc(h, &h->sel_state, 3 * MAX_TABLES));  // v* prefix, slots to take, arrivals
     TRY(dalloc(h, &h->sel_hist, (int64_t)MAX_TABLES * SEL_BINS));
+    TRY(dalloc(h, &h->sel_key, S));
     TRY(dalloc(h, &h->partial, nchunk_max * h->D));
     h->stage_rows = std::min<int64_t>(NM, S);
     h->nstage = MAX_NSTAGE;
@@ -1964,7 +1966,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
         else
             launch_select_victims(a, levels, maxS, h->hold_to, h->held, h->sel_state, h->sel_hist, h->vk0,
                                   h->vv0, h->vk1, (uint32_t *)nullptr, n_miss, h->hist,
-                                  h->ws_plan, tk.v_slot, &h->cnt->err_sticky, h->s_plan);
+                                  h->sel_key, h->ws_plan, tk.v_slot, &h->cnt->err_sticky, h->s_plan);
     }
     WindowKeys wk{};
     wk.n = nhold;

@@ -704,12 +704,13 @@ struct VictimOut {
 
 // ---------------------------------------------------------------- victim order in LDS
 //
-// When every active table has at most VS_MAX victims, one block per table puts
-// its compacted victims (slot order) into priority order: the stable LDS radix
-// sort on entries (priority << 32 | slot), keyed on the priority bits only.
+// When every active table has at most VS_MAX victims (but some table more slots
+// than k_select_one takes), one block per table puts its compacted victims
+// (slot order) into priority order: the stable LDS radix sort on entries
+// (priority << 32 | slot), keyed on the priority bits only.
 constexpr int VS_THREADS = 1024;
 constexpr int VS_WAVES = VS_THREADS / WAVE;
-constexpr int VS_MAX = 2048;
+constexpr int VS_MAX = 8192;
 
 __global__ void __launch_bounds__(VS_THREADS) k_victim_sort(SelArgs a, const uint32_t *vk,
                                                           const uint32_t *vv, int32_t *v_slot)
@@ -728,6 +729,172 @@ __global__ void __launch_bounds__(VS_THREADS) k_victim_sort(SelArgs a, const uin
     const uint64_t *srt = lds_radix_sort<VS_THREADS, VS_MAX / VS_THREADS>(
         eb[0], eb[1], n, 32, a.prio_bits, wc, lds);
     for (int i = tid; i < n; i += VS_THREADS) v_slot[off + i] = (int32_t)(uint32_t)srt[i];
+}
+
+// The whole choice in one launch, one block per table: for tables of at most
+// SELECT_ONE_SLOTS slots and VS_MAX victims.  The block writes each slot's
+// priority (or HELD) to skey while it counts the first digit, finds the
+// threshold digit by digit as k_sel_level does, compacts the slots below it in
+// slot order into LDS (each wave its own contiguous share, ballot by ballot)
+// and sorts them there.  A block reads a slot's twelve bytes once and four
+// bytes per further step, so one compute unit bounds it, at some 1.4 us per
+// thousand slots: 2048 slots 13.7 us (the launches it replaces, a level or more
+// of the select over all tables, the segmented scan and the sort, 8.4 + 9.8 +
+// 5.2 us and two more launches), 9000 slots 23 us (11.4 + 11.4 + 5.2), 100k
+// slots 146 us (25 + 17 + 7).
+constexpr int64_t SELECT_ONE_SLOTS = 16 << 10;
+constexpr uint32_t KEY_HELD = 0xFFFFFFFFu;  // priorities are below 2^31
+
+// h[bin] += 1 for the lanes with `valid`.  Neighbouring slots were often filled
+// by one plan and share their priority, so a few rounds add whole groups of
+// equal bins; what is left adds lane by lane.
+__device__ __forceinline__ void wave_hist(uint32_t *h, uint32_t bin, bool valid)
+{
+    uint64_t todo = __ballot(valid);
+#pragma unroll
+    for (int r = 0; r < 3 && todo; ++r) {
+        const int leader = __ffsll((unsigned long long)todo) - 1;
+        const uint32_t lb = __shfl(bin, leader, WAVE);
+        const uint64_t same = __ballot(valid && bin == lb) & todo;
+        if (lane_id() == leader) atomicAdd(&h[lb], (uint32_t)__popcll(same));
+        todo &= ~same;
+    }
+    if ((todo >> lane_id()) & 1ull) atomicAdd(&h[bin], 1u);
+}
+
+__global__ void __launch_bounds__(VS_THREADS) k_select_one(SelArgs a, int levels,
+                                                           const int32_t *hold_to,
+                                                           const int32_t *held, uint32_t *skey,
+                                                           int32_t *v_slot, int32_t *err)
+{
+    constexpr int U = 8;  // slots per thread and round, loads in flight together
+    __shared__ uint64_t eb[2][VS_MAX];
+    __shared__ uint32_t wc[VS_WAVES][256];
+    __shared__ uint32_t lds[VS_WAVES];
+    __shared__ uint32_t pick_s[2];  // threshold prefix, slots still to take
+    __shared__ uint32_t bits_s;
+    uint32_t *const h = reinterpret_cast<uint32_t *>(eb);  // the levels' histogram
+    const int y = blockIdx.x, tid = threadIdx.x, lane = lane_id(), w = wave_id();
+    const int64_t base = a.base[y];
+    const int S = (int)a.S[y];
+    const int k = a.k[y] < VS_MAX ? a.k[y] : VS_MAX;
+    uint32_t *const key_of = skey + base;
+    if (tid == 0) {
+        pick_s[0] = 0;
+        pick_s[1] = (uint32_t)k;
+        bits_s = 0;
+    }
+    for (int l = 0; l < levels; ++l) {
+        const int shift = (levels - 1 - l) * SEL_BITS;
+        for (int b = tid; b < SEL_BINS; b += VS_THREADS) h[b] = 0;
+        __syncthreads();
+        const uint32_t prefix = pick_s[0], krem = pick_s[1];
+        for (int s0 = 0; s0 < S; s0 += VS_THREADS * U) {
+            uint32_t key[U];
+            if (l == 0) {
+                int32_t hv[U], sv[U], lv[U];
+#pragma unroll
+                for (int r = 0; r < U; ++r) {
+                    const int s = s0 + r * VS_THREADS + tid;
+                    hv[r] = s < S ? hold_to[base + s] : a.plan;
+                    sv[r] = s < S ? held[base + s] : a.stamp;
+                    lv[r] = s < S ? a.prio.src[base + s] : 0;
+                }
+#pragma unroll
+                for (int r = 0; r < U; ++r) {
+                    const int s = s0 + r * VS_THREADS + tid;
+                    const bool free = hv[r] < a.plan && sv[r] != a.stamp;
+                    key[r] = free ? a.prio.key(lv[r], base + s) : KEY_HELD;
+                    if (s < S) key_of[s] = key[r];
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < U; ++r) {
+                    const int s = s0 + r * VS_THREADS + tid;
+                    key[r] = s < S ? key_of[s] : KEY_HELD;  // its own store
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < U; ++r) {
+                const bool in = key[r] != KEY_HELD && (uint64_t)key[r] >> (shift + SEL_BITS) ==
+                                                          (uint64_t)prefix >> (shift + SEL_BITS);
+                wave_hist(h, (key[r] >> shift) & (SEL_BINS - 1), in);
+            }
+        }
+        __syncthreads();
+        constexpr int PER = SEL_BINS / VS_THREADS;
+        uint32_t c[PER], sum = 0, total;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) sum += c[q] = h[tid * PER + q];
+        uint32_t cum = block_excl_scan_n<VS_THREADS>(sum, lds, total);
+        if (cum < krem && krem <= cum + sum) {
+#pragma unroll
+            for (int q = 0; q < PER; ++q) {
+                if (cum + c[q] >= krem) {
+                    pick_s[0] = prefix | (uint32_t)(tid * PER + q) << shift;
+                    pick_s[1] = krem - cum;
+                    break;
+                }
+                cum += c[q];
+            }
+        }
+        __syncthreads();
+    }
+    const uint32_t vstar = pick_s[0], take = pick_s[1];  // below it all, of the equal ones `take`
+    // ---- compaction in slot order: wave w owns slots [b, z)
+    const int per = ((S + VS_WAVES - 1) / VS_WAVES + WAVE - 1) / WAVE * WAVE;
+    const int b = w * per < S ? w * per : S, z = b + per < S ? b + per : S;
+    uint32_t nb = 0, ne = 0;
+#pragma unroll 4
+    for (int s0 = b; s0 < z; s0 += WAVE) {
+        const uint32_t key = s0 + lane < z ? key_of[s0 + lane] : KEY_HELD;
+        nb += (uint32_t)__popcll(__ballot(key < vstar));
+        ne += (uint32_t)__popcll(__ballot(key == vstar));
+    }
+    if (lane == 0) {
+        wc[0][w] = nb;
+        wc[1][w] = ne;
+    }
+    __syncthreads();
+    uint32_t below = 0, eq = 0, all_b = 0, all_e = 0;
+    for (int q = 0; q < VS_WAVES; ++q) {
+        if (q < w) {
+            below += wc[0][q];
+            eq += wc[1][q];
+        }
+        all_b += wc[0][q];
+        all_e += wc[1][q];
+    }
+    const uint32_t found = all_b + (all_e < take ? all_e : take);
+    const int n = found < (uint32_t)k ? (int)found : k;
+    if (n < a.k[y] && tid == 0) atomicOr(err, ERR_PLAN);  // every miss must get a slot
+    __syncthreads();  // wc is read; h (in eb) as well, before the entries go there
+    const uint64_t lt = lanemask_lt();
+    uint32_t diff = 0;
+#pragma unroll 4
+    for (int s0 = b; s0 < z; s0 += WAVE) {
+        const uint32_t key = s0 + lane < z ? key_of[s0 + lane] : KEY_HELD;
+        const uint64_t bb = __ballot(key < vstar), be = __ballot(key == vstar);
+        const uint32_t mb = below + (uint32_t)__popcll(bb & lt);
+        const uint32_t me = eq + (uint32_t)__popcll(be & lt);
+        const uint32_t pos = mb + (me < take ? me : take);
+        if ((key < vstar || (key == vstar && me < take)) && pos < (uint32_t)k) {
+            eb[0][pos] = (uint64_t)key << 32 | (uint32_t)(base + s0 + lane);
+            diff |= key ^ vstar;
+        }
+        below += (uint32_t)__popcll(bb);
+        eq += (uint32_t)__popcll(be);
+    }
+    // the highest bit in which two of the priorities differ bounds the sort
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) diff |= __shfl_xor(diff, o, WAVE);
+    if (lane == 0 && diff) atomicOr(&bits_s, diff);
+    __syncthreads();
+    const int bits = bits_s ? 32 - __clz((int)bits_s) : 0;
+    const uint64_t *srt = lds_radix_sort<VS_THREADS, VS_MAX / VS_THREADS>(eb[0], eb[1], n, 32, bits,
+                                                                          wc, lds);
+    for (int i = tid; i < a.k[y]; i += VS_THREADS)
+        v_slot[a.vbase[y] + i] = i < n ? (int32_t)(uint32_t)srt[i] : -1;
 }
 
 // Victims when every table's misses fit in its never-used slots.  Those slots
@@ -757,8 +924,8 @@ void launch_fresh_victims(const FreshArgs &f, int64_t max_k, int32_t *v_slot, hi
 void launch_select_victims(const SelArgs &a, int levels, int64_t maxS, const int32_t *hold_to,
                            const int32_t *held, int32_t *sel_state, int32_t *sel_hist,
                            uint32_t *vk0, uint32_t *vv0, uint32_t *vk1, uint32_t *vv1,
-                           int64_t n_victims, uint32_t *hist, ScanWs &ws, int32_t *v_slot,
-                           int32_t *err, hipStream_t s)
+                           int64_t n_victims, uint32_t *hist, uint32_t *skey, ScanWs &ws,
+                           int32_t *v_slot, int32_t *err, hipStream_t s)
 {
     if (a.nact <= 0 || n_victims <= 0) return;
     // small victim sets are ordered per table in LDS; otherwise one global
@@ -766,6 +933,16 @@ void launch_select_victims(const SelArgs &a, int levels, int64_t maxS, const int
     // pass will end in v_slot
     bool small = true;
     for (int y = 0; y < a.nact; ++y) small = small && a.k[y] <= VS_MAX;
+    if (small && maxS <= SELECT_ONE_SLOTS) {
+        hipLaunchKernelGGL(k_select_one, dim3(a.nact), dim3(VS_THREADS), 0, s, a, levels, hold_to,
+                           held, skey, v_slot, err);
+        return;
+    }
+    // four LDS passes over thousands of victims (random priorities) take one
+    // block longer than the global sort's passes: 16 tables of 200k rows, 5.6k
+    // victims each, a step 0.39 ms against 0.38
+    for (int y = 0; y < a.nact; ++y)
+        small = small && (a.k[y] <= VS_MAX / 4 || a.prio_bits <= 16);
     const int bits = a.act_bits + a.prio_bits;
     const int passes = small ? 1 : radix_passes(n_victims, bits);
     uint32_t *ck = (passes & 1) ? vk0 : vk1;

@@ -320,8 +320,8 @@ void launch_fresh_victims(const FreshArgs &f, int64_t max_k, int32_t *v_slot, hi
 void launch_select_victims(const SelArgs &a, int levels, int64_t maxS, const int32_t *hold_to,
                            const int32_t *held, int32_t *sel_state, int32_t *sel_hist,
                            uint32_t *vk0, uint32_t *vv0, uint32_t *vk1, uint32_t *vv1,
-                           int64_t n_victims, uint32_t *hist, ScanWs &ws, int32_t *v_slot,
-                           int32_t *err, hipStream_t s);
+                           int64_t n_victims, uint32_t *hist, uint32_t *skey, ScanWs &ws,
+                           int32_t *v_slot, int32_t *err, hipStream_t s);
 // The window batches' sorted unique keys (0 = the planned batch), for the
 // hold of filled rows.  fast: at most one batch enters (at window index ent,
 // 0 if none) and the holds were not rebuilt, so lastq / pend (with this
