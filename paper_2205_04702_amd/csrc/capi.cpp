@@ -370,8 +370,6 @@ constexpr int64_t SMALL_COPY_BYTES = 8ll << 20;
 // most of a step (5 ms and more on the host link): batches prepared ahead are
 // then sorted behind the update instead of behind it.
 constexpr int64_t DEFER_BEHIND_COPY_BYTES = 256ll << 20;
-// device-to-host copies of write-backs are issued in pieces of this size
-constexpr int64_t WB_PIECE_BYTES = 32ll << 20;
 
 struct sp_ctx {
     // configuration
@@ -477,9 +475,9 @@ struct sp_ctx {
     // staging of evicted rows, plan p in slot p % nstage: n rows, then their n
     // previous keys.  Plan p's copy to the host is issued by plan p + 1 (or by
     // flush), when its fill has nearly always finished: copy_pending = p
-    float *stage_dev[MAX_NSTAGE]{}, *stage_host[MAX_NSTAGE]{};
+    float *stage_dev[MAX_NSTAGE]{}, *stage_host[MAX_NSTAGE]{}, *stage_hdev[MAX_NSTAGE]{};
     // mapped fill: the move kernel writes the evicted rows straight to the
-    // pinned staging (stage_dev is its device-visible address), slot
+    // pinned staging (stage_dev is stage_hdev, its device-visible address), slot
     // fills % nstage; slot_ticket: the last plan whose rows are in the slot
     int64_t fills = 0;
     int64_t slot_ticket[MAX_NSTAGE]{-1, -1, -1};
@@ -1076,9 +1074,11 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     h->stage_rows = std::min<int64_t>(NM, S);
     h->nstage = MAX_NSTAGE;
     for (int i = 0; i < h->nstage; ++i) {
-        TRY(palloc(h, &h->stage_host[i], h->stage_rows * (h->D + 1)));
-        if (h->staged) TRY(dalloc(h, &h->stage_dev[i], h->stage_rows * (h->D + 1)));
-        else HIPCHK(nullptr, hipHostGetDevicePointer((void **)&h->stage_dev[i], h->stage_host[i], 0));
+        // (whole 16-byte words: the write-back copies such)
+        TRY(palloc(h, &h->stage_host[i], h->stage_rows * (h->D + 1) + 4));
+        HIPCHK(nullptr, hipHostGetDevicePointer((void **)&h->stage_hdev[i], h->stage_host[i], 0));
+        if (h->staged) TRY(dalloc(h, &h->stage_dev[i], h->stage_rows * (h->D + 1) + 4));
+        else h->stage_dev[i] = h->stage_hdev[i];
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ev_d2h[i], hipEventDisableTiming));
         if (h->staged) {  // at most min(misses, slots) rows per plan, like the write-back
             {  // device-mapped: the query writes the missing keys here itself
@@ -1402,18 +1402,8 @@ static sp_status issue_copy(sp_ctx *h, hipStream_t s)
     const int64_t n = h->copy_n;
     if (n > 0) {
         HIPCHK(h, wait_unless_done(s, h->ev_filled[p % h->nring]));
-        // in pieces: the runtime copies device to host with a blit kernel
-        // that keeps a workgroup on every compute unit until it ends, and
-        // one copy of a large write-back runs for most of the step; pieces
-        // end often enough for the training kernels' workgroups to take
-        // those units (the 26x10M update: 0.63 ms beside pieces of 32 MiB,
-        // 0.74-0.84 ms beside one copy of 911 MB)
-        const int64_t bytes = (int64_t)sizeof(float) * n * (h->D + 1);
-        for (int64_t off = 0; off < bytes; off += WB_PIECE_BYTES)
-            HIPCHK(h, hipMemcpyAsync((char *)h->stage_host[sl] + off,
-                                     (const char *)h->stage_dev[sl] + off,
-                                     std::min(WB_PIECE_BYTES, bytes - off),
-                                     hipMemcpyDeviceToHost, s));
+        launch_push(h->stage_dev[sl], h->stage_hdev[sl], (int64_t)sizeof(float) * n * (h->D + 1), s);
+        CHECK_LAUNCH(h);
         HIPCHK(h, hipEventRecord(h->ev_d2h[sl], s));
         job.ev = h->ev_d2h[sl];
         job.rows = h->stage_host[sl];

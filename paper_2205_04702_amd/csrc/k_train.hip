@@ -53,46 +53,29 @@ __device__ __forceinline__ float4 reduce_rows(float4 acc)
     return acc;
 }
 
-// Sum of the rows src[slot_u[inv[k]]] for k in [beg, end), one wave: inv read
-// 64 at a time (coalesced), the slots gathered (one table's few unique keys,
-// which stay in L2) and broadcast by shuffles; each lane group takes every
-// RPP-th row in order and UNROLL rows are in flight per lane.
-template <int LPR, int UNROLL>
-__device__ __forceinline__ float4 gather_sum(const float4 *__restrict__ src, int64_t nrows,
-                                             const int32_t *__restrict__ inv,
-                                             const int32_t *__restrict__ slot_u, int64_t n_unique,
-                                             int64_t beg, int64_t end)
-{
-    constexpr int RPP = WAVE / LPR;
-    const int lane = lane_id(), sub = lane / LPR, c = lane % LPR;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int64_t base = beg; base < end; base += WAVE) {
-        const int n = (int)((end - base) < WAVE ? (end - base) : WAVE);
-        const int32_t ui = lane < n ? inv[base + lane] : 0;
-        const int32_t my = slot_u[(uint32_t)ui < (uint64_t)n_unique ? ui : 0];
-        for (int k0 = 0; k0 < n; k0 += RPP * UNROLL) {
-            float4 v[UNROLL];
-#pragma unroll
-            for (int q = 0; q < UNROLL; ++q) {
-                const int k = k0 + q * RPP + sub;
-                int32_t r = __shfl(my, k < n ? k : 0, WAVE);
-                r = (uint32_t)r < (uint64_t)nrows ? r : 0;  // never leave the array
-                v[q] = k < n ? src[(int64_t)r * LPR + c] : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int q = 0; q < UNROLL; ++q) acc = f4_add(acc, v[q]);
-        }
-    }
-    return acc;
-}
-
 // ---------------------------------------------------------------- forward
 
 // out[g] = sum of Storage[slot_u[inv[j]]] over the positions j of bag g
-// (Sec. II-B, gather then element-wise reduction per table).  One wave per bag.
-// Reading each position's slot through its unique key costs a wave one more
-// round trip per 64 positions, hidden behind the other waves, and spares the
-// plan a pass that writes a slot per position (it was most of a large commit).
+// (Sec. II-B, gather then element-wise reduction per table).  Reading each
+// position's slot through its unique key costs one more round trip per block
+// of positions, hidden behind the other waves, and spares the plan a pass that
+// writes a slot per position (it was most of a large commit).
+//
+// One group of GW lanes per bag: as many as a row has words, eight at least
+// (then several rows at a time).  A bag is a chain of dependent loads (offsets,
+// unique keys, slots, rows), which is what bounds this kernel where the rows
+// come from L2, so the more bags a wave works on at once the better: with one
+// wave per bag, 53k bags of four rows of 64 floats took 19 us, 12 now; 53k bags
+// of one row of 16 floats 18 us, 7 now.  Large batches of long bags are bound
+// by their rows instead: 524k bags of 40 rows of 64 floats 0.43 ms, 0.40 now
+// (13.7 TB/s of requests); 106k bags of 40 rows of 128 floats 0.195 ms as
+// before (11.2 TB/s of requests, a quarter of them distinct rows).  The group reads IB positions' slots at a time (the next ones while this block's
+// rows arrive) and broadcasts them by shuffles, FWD_ROWS row loads in flight
+// per lane.  Sums run over FWD_ACC partial sums in position order.
+constexpr int FWD_ROWS = 8;
+constexpr int FWD_ACC = 4;
+constexpr int fwd_lanes(int lpr) { return lpr < 8 ? 8 : lpr; }
+
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ storage,
                                                    const int32_t *__restrict__ inv,
@@ -102,16 +85,83 @@ __global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ st
                                                    int64_t nbags, int64_t nslots,
                                                    float4 *__restrict__ out)
 {
+    constexpr int GW = fwd_lanes(LPR);
+    constexpr int RPG = GW / LPR;                     // rows per load of a group
+    constexpr int BATCH = RPG * FWD_ROWS;             // positions per batch of loads
+    constexpr int IPL = BATCH > GW ? BATCH / GW : 1;  // positions held per lane
+    constexpr int IB = IPL * GW;                      // positions per block
     // consecutive bags (one table's) on one XCD: the table's hot rows share its L2
-    const int64_t g = xcd_block(blockIdx.x, gridDim.x) * (BLOCK / WAVE) + wave_id();
-    if (g >= nbags) return;
-    // at least 8 rows in flight per wave (a wave covers 64/LPR rows per load)
-    constexpr int UNROLL = LPR >= 32 ? 8 : 4;
-    float4 acc = gather_sum<LPR, UNROLL>(storage, nslots, inv, slot_u, n_unique, bag_off[g],
-                                         bag_off[g + 1]);
-    acc = reduce_rows<LPR>(acc);
-    const int lane = lane_id();
-    if (lane < LPR) out[g * LPR + lane] = acc;
+    const int64_t g = (xcd_block(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x) / GW;
+    const int lane = lane_id(), gl = lane % GW, g0 = lane - gl;
+    const int sub = gl / LPR, c = gl % LPR;
+    int64_t beg = 0, end = 0;
+    if (g < nbags) {
+        beg = bag_off[g];
+        end = bag_off[g + 1];
+    }
+    const int64_t len = end - beg > 0 ? end - beg : 0;
+    // the wave's longest bag: all groups walk as far
+    int64_t longest = len;
+#pragma unroll
+    for (int o = GW; o < WAVE; o <<= 1) {
+        const int64_t x = __shfl_xor((int32_t)longest, o, WAVE);
+        longest = x > longest ? x : longest;
+    }
+    float4 acc[FWD_ACC];
+#pragma unroll
+    for (int k = 0; k < FWD_ACC; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+    int32_t ui[IPL], slot[IPL];
+    auto load_unique = [&](int64_t base) {  // lane gl holds positions base + l * GW + gl
+#pragma unroll
+        for (int l = 0; l < IPL; ++l) {
+            const int64_t k = base + l * GW + gl;
+            ui[l] = k < len ? inv[beg + k] : 0;
+        }
+    };
+    auto load_slots = [&](int64_t base) {
+#pragma unroll
+        for (int l = 0; l < IPL; ++l) {
+            const int64_t k = base + l * GW + gl;
+            const int32_t r = k < len ? slot_u[(uint32_t)ui[l] < (uint64_t)n_unique ? ui[l] : 0] : 0;
+            slot[l] = (uint32_t)r < (uint64_t)nslots ? r : 0;  // never leave the array
+        }
+    };
+    load_unique(0);
+    load_slots(0);
+    for (int64_t base = 0; base < longest; base += IB) {
+        const int n = (int)(len - base < IB ? (len - base < 0 ? 0 : len - base) : IB);
+        const int most = (int)(longest - base < IB ? longest - base : IB);
+        int32_t cur[IPL];
+#pragma unroll
+        for (int l = 0; l < IPL; ++l) cur[l] = slot[l];
+        const bool more = base + IB < longest;
+        if (more) load_unique(base + IB);
+#pragma unroll
+        for (int k0 = 0; k0 < IB; k0 += BATCH) {
+            if (k0 >= most) break;  // uniform over the wave
+            float4 v[FWD_ROWS];
+#pragma unroll
+            for (int q = 0; q < FWD_ROWS; ++q) {
+                v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (q * RPG + k0 >= most) continue;  // uniform
+                const int k = k0 + q * RPG + sub;
+                // position k is held by lane k % GW of the group; with several rows
+                // per load, k / GW is the same for all of them
+                const int32_t r = __shfl(cur[(k0 + q * RPG) / GW], g0 + k % GW, WAVE);
+                if (k < n) v[q] = storage[(int64_t)r * LPR + c];
+            }
+            if (k0 == 0 && more) load_slots(base + IB);  // behind this batch's rows
+#pragma unroll
+            for (int q = 0; q < FWD_ROWS; ++q) acc[q % FWD_ACC] = f4_add(acc[q % FWD_ACC], v[q]);
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < FWD_ACC; o <<= 1)
+#pragma unroll
+        for (int k = 0; k < FWD_ACC; k += 2 * o) acc[k] = f4_add(acc[k], acc[k + o]);
+#pragma unroll
+    for (int o = LPR; o < GW; o <<= 1) acc[0] = f4_add(acc[0], f4_xor(acc[0], o));
+    if (g < nbags && sub == 0) out[g * LPR + c] = acc[0];
 }
 
 // ---------------------------------------------------------------- backward + SGD
@@ -423,6 +473,47 @@ __global__ void __launch_bounds__(BLOCK) k_move(float4 *__restrict__ storage, Ta
     }
 }
 
+// The write-back's copy to pinned host memory, by a few blocks of one XCD
+// (block b runs on XCD b % 8; the others leave at once).  The host link takes
+// 56 GB/s, which four blocks already reach; stores beyond that only wait, and
+// they wait in the XCD's path to memory in front of every other kernel's
+// accesses there.  Measured beside an update-like kernel (scattered rows of 512
+// bytes, 224 us alone) with 66 MB on the way: 8 blocks over all XCDs hold it to
+// 663 us and 256 blocks to 1182 us, as the runtime's copy kernel did (an update
+// of 0.15 ms took 1.4 ms in the 8x400k x 128 workload, all of the copy's
+// length); 8 blocks on one XCD leave it at 245 us and reach 55 GB/s alone.
+constexpr int PUSH_BLOCKS = 8;
+constexpr int PUSH_WORDS = 4;
+
+__global__ void __launch_bounds__(BLOCK) k_push(const float4 *__restrict__ src,
+                                                float4 *__restrict__ dst, int64_t words)
+{
+    if (blockIdx.x % XCDS) return;
+    constexpr int64_t stride = (int64_t)PUSH_BLOCKS * BLOCK;
+    for (int64_t i0 = (int64_t)(blockIdx.x / XCDS) * BLOCK + threadIdx.x; i0 < words;
+         i0 += stride * PUSH_WORDS) {
+        nv4f v[PUSH_WORDS];
+#pragma unroll
+        for (int q = 0; q < PUSH_WORDS; ++q) {
+            const int64_t i = i0 + q * stride;
+            v[q] = nt_row(src + (i < words ? i : i0));
+        }
+#pragma unroll
+        for (int q = 0; q < PUSH_WORDS; ++q) {
+            const int64_t i = i0 + q * stride;
+            if (i < words) nt_row_store(dst + i, v[q]);
+        }
+    }
+}
+
+void launch_push(const void *src, void *dst, int64_t bytes, hipStream_t s)
+{
+    const int64_t words = (bytes + 15) / 16;
+    if (words <= 0) return;
+    hipLaunchKernelGGL(k_push, dim3(PUSH_BLOCKS * XCDS), dim3(BLOCK), 0, s, (const float4 *)src,
+                       (float4 *)dst, words);
+}
+
 // ---------------------------------------------------------------- fixed scratch
 
 // Partial sums of split runs for callers that cannot allocate: a fixed array
@@ -491,7 +582,8 @@ void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t
                     hipEvent_t e0, hipEvent_t e1)
 {
     if (nbags <= 0) return;
-    SP_DISPATCH_LPR_EV(dim / 4, k_forward, grid_waves(nbags), e0, e1, (const float4 *)storage,
+    SP_DISPATCH_LPR_EV(dim / 4, k_forward, grid_rows(nbags, fwd_lanes(dim / 4)), e0, e1,
+                       (const float4 *)storage,
                        inv, slot_u, n_unique, bag_off, nbags, nslots, (float4 *)out);
 }
 

@@ -360,6 +360,9 @@ void launch_pf_arrange(const Tables &tb, PrefetchDev pf, int64_t n_own,
 // staged fill), else straight from the mapped host table.
 void launch_move(float *storage, int dim, const Tables &tb, float *const *host_dev, TicketDev tk,
                  int64_t n_miss, int32_t u, float *stage, const float *staged, hipStream_t s);
+// Copies bytes (rounded up to whole 16-byte words; both ends 16-byte aligned)
+// from device memory to pinned host memory (its device-visible address).
+void launch_push(const void *src, void *dst, int64_t bytes, hipStream_t s);
 void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *inv,
                     const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
                     hipEvent_t e0, hipEvent_t e1);
