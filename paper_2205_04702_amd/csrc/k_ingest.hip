@@ -106,8 +106,8 @@ __global__ void __launch_bounds__(BLOCK) k_bags(const int32_t *bag_off, int32_t 
 //    entries with wave ballots, puts them in digit order in LDS and writes
 //    each digit's entries as one run.
 // What bounds it: HBM traffic, 8 bytes read and written per entry and pass
-// plus 8 for the counts: alone a pass takes 0.11 + 0.10 ms for 21M IDs and
-// 0.042 + 0.042 ms for 4.3M.  Before (11-bit digits of the whole key, entries
+// plus 8 for the counts: alone a pass takes 0.05 + 0.10 ms for 21M IDs and
+// 0.02 + 0.03 ms for 4.3M.  Before (11-bit digits of the whole key, entries
 // scattered one by one to 2048 bins, a scan launch per pass) 21M IDs took 3
 // passes of 0.43 ms, 4.3M IDs 2 of 0.38 ms.
 constexpr int SORT_BITS = 9;
@@ -161,18 +161,29 @@ __device__ __forceinline__ bool sort_digit(int64_t rows, int q, int passes, int 
     return p >= 0;
 }
 
-// Entry i of a table: its ID as an entry, or the entry an earlier pass left.
-__device__ __forceinline__ uint64_t sort_entry(bool first, const int32_t *ids, const uint64_t *in,
-                                               int64_t i, int t, int row_bits, int64_t rows,
-                                               bool &bad)
+// ITEMS entries of a table, at(r) clamped into its span by the caller: its IDs
+// as entries, or what an earlier pass left.  No branch around a load, so all
+// are in flight together.
+template <int ITEMS, class At>
+__device__ __forceinline__ void sort_entries(uint64_t (&e)[ITEMS], bool first, const int32_t *ids,
+                                             const uint64_t *in, int t, int row_bits, int64_t rows,
+                                             At at, bool &bad)
 {
-    if (!first) return in[i];
-    int32_t row = ids[i];
-    if (row < 0 || (int64_t)row >= rows) {
-        bad = true;
-        row = 0;
+    if (first) {  // uniform over the block
+        int32_t row[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) row[r] = ids[at(r)];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const bool out = row[r] < 0 || (int64_t)row[r] >= rows;
+            bad |= out;
+            const uint32_t key = ((uint32_t)t << row_bits) | (uint32_t)(out ? 0 : row[r]);
+            e[r] = (uint64_t)key << 32 | (uint64_t)(uint32_t)at(r);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) e[r] = in[at(r)];
     }
-    return (uint64_t)(((uint32_t)t << row_bits) | (uint32_t)row) << 32 | (uint64_t)(uint32_t)i;
 }
 
 // NT * ITEMS entries per tile.  Blocks past `groups` of the first launch mark
@@ -222,17 +233,17 @@ __global__ void __launch_bounds__(NT) k_sort_hist(Tables tb, const int32_t *ids,
     uint32_t sum[PER] = {};
     for (int tile = tile_a; tile < tile_b; ++tile) {
         const int64_t base = (int64_t)lay.beg[t] + (int64_t)(tile - lay.tile0[t]) * TILE;
-        uint32_t key[ITEMS];
-#pragma unroll
-        for (int r = 0; r < ITEMS; ++r) {
-            const int64_t i = base + r * NT + tid;
-            key[r] = 0;
-            if (i < end)
-                key[r] = (uint32_t)(sort_entry(first, ids, in, i, t, tb.row_bits, rows, bad) >> 32);
-        }
+        uint64_t e[ITEMS];
+        sort_entries(e, first, ids, in, t, tb.row_bits, rows,
+                     [&](int r) {
+                         const int64_t i = base + r * NT + tid;
+                         return i < end ? i : end - 1;
+                     },
+                     bad);
 #pragma unroll
         for (int r = 0; r < ITEMS; ++r)
-            if (base + r * NT + tid < end) atomicAdd(&h[(key[r] >> shift) & mask], 1u);
+            if (base + r * NT + tid < end)
+                atomicAdd(&h[(uint32_t)(e[r] >> (32 + shift)) & mask], 1u);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
@@ -294,11 +305,12 @@ __global__ void __launch_bounds__(NT) k_sort_scatter(Tables tb, const int32_t *i
     const int n = (int)(end - base < TILE ? end - base : TILE);
     // wave w holds its own contiguous share of the tile, 64 entries at a time
     uint64_t e[ITEMS];
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        const int i = w * (ITEMS * WAVE) + r * WAVE + lane;
-        e[r] = i < n ? sort_entry(first, ids, in, base + i, t, tb.row_bits, rows, bad) : 0ull;
-    }
+    sort_entries(e, first, ids, in, t, tb.row_bits, rows,
+                 [&](int r) {
+                     const int i = w * (ITEMS * WAVE) + r * WAVE + lane;
+                     return base + (i < n ? i : n - 1);
+                 },
+                 bad);
     // thread tid owns digits tid * PER ..: the table's entries of each digit,
     // and those in tiles before this one
     uint32_t total[PER] = {}, before[PER] = {};
@@ -409,8 +421,9 @@ __global__ void __launch_bounds__(NT) k_sort_scatter(Tables tb, const int32_t *i
 // per sorted entry the bag (sbag) and the run of its position (inv).  The
 // second reading of the entries (8 bytes each) buys tiles that need no order
 // among them, so consecutive tiles stay on one XCD and the scattered stores of
-// inv, which stay within a table's span, meet in its L2: 0.10 + 0.48 ms for
-// 21M IDs, 0.03 + 0.07 ms for 4.3M.  Before, two single-pass scans did this in 0.9 + 1.2 ms for 21M IDs and 0.22 + 0.70 ms
+// inv, which stay within a table's span, meet in its L2: 0.10 + 0.38 ms for
+// 21M IDs, 0.04 + 0.07 ms for 4.3M (42M scattered 4-byte accesses in L2 bound
+// the second).  Before, two single-pass scans did this in 0.9 + 1.2 ms for 21M IDs and 0.22 + 0.70 ms
 // for 4.3M: the stores of a line came from all XCDs, every descriptor was
 // stored by a serial loop, and every long run took an atomic on one address.
 constexpr uint32_t KEY_PAST = 0xFFFFFFFFu;  // after the last entry (keys are below 2^31)
@@ -439,6 +452,10 @@ __device__ __forceinline__ int64_t run_start(const uint64_t *e, int64_t i, uint3
     }
 }
 
+// LDS place of index i: threads own eight consecutive entries each, and one
+// word of padding per eight puts their accesses on different banks.
+constexpr __host__ __device__ int run_lds(int i) { return i + (i >> 3); }
+
 template <int NT, int ITEMS, bool EMIT>
 __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *bag_off, int32_t T,
                                              int32_t B, int64_t nnz, const int32_t *bag_of,
@@ -448,8 +465,8 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
 {
     constexpr int TILE = NT * ITEMS;
     constexpr int HALO = BWD_CHUNK;
-    __shared__ uint32_t key[1 + TILE + HALO];  // key[1 + i]: entry i of the tile
-    __shared__ uint32_t pos[EMIT ? TILE : 1], seg[EMIT ? TILE : 1];
+    __shared__ uint32_t key[run_lds(1 + TILE + HALO)];  // at run_lds(1 + i): entry i of the tile
+    __shared__ uint32_t pos[EMIT ? TILE : 1], seg[EMIT ? run_lds(TILE) : 1];
     __shared__ uint64_t lds[NT / WAVE];
     __shared__ int32_t ldsm[NT / WAVE];
     __shared__ int64_t start_s;
@@ -471,16 +488,30 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
     __syncthreads();
     const int64_t total = total_s;
     const int n = (int)(total - base < 0 ? 0 : (total - base < TILE ? total - base : TILE));
-    for (int i = tid; i < 1 + TILE + HALO; i += NT) {
-        const int64_t g = base + i - 1;
-        const uint64_t x = g >= 0 && g < total ? e[g] : (uint64_t)KEY_PAST << 32;
-        key[i] = (uint32_t)(x >> 32);
-        if (EMIT && i >= 1 && i <= TILE) pos[i - 1] = (uint32_t)x;
+    {
+        // the tile's entries, the one before it and HALO after, all in flight
+        // together (indices clamped, values past the last entry replaced)
+        auto entry = [&](int64_t g) {
+            const uint64_t x = __builtin_nontemporal_load(
+                &e[g < 0 ? 0 : (g < total ? g : (total > 0 ? total - 1 : 0))]);
+            return g >= 0 && g < total ? x : (uint64_t)KEY_PAST << 32;
+        };
+        uint64_t x[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) x[r] = entry(base + r * NT + tid);
+        const int hi = tid == 0 ? 0 : TILE + tid;  // entry before the tile, then the halo
+        const uint64_t y = entry(base + hi - 1);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            key[run_lds(1 + r * NT + tid)] = (uint32_t)(x[r] >> 32);
+            if (EMIT) pos[r * NT + tid] = (uint32_t)x[r];
+        }
+        if (tid <= HALO) key[run_lds(hi)] = (uint32_t)(y >> 32);
     }
     __syncthreads();
     if (tid < WAVE) {  // where the run that reaches into the tile starts
         int64_t s = base;
-        if (n > 0 && base > 0 && key[0] == key[1]) s = run_start(e, base, key[1]);
+        if (n > 0 && base > 0 && key[run_lds(0)] == key[run_lds(1)]) s = run_start(e, base, key[run_lds(1)]);
         if (tid == 0) start_s = s;
     }
     // thread tid owns entries tid * ITEMS ..
@@ -489,7 +520,7 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int i = tid * ITEMS + k;
-        if (i < n && (base + i == 0 || key[i] != key[1 + i])) {
+        if (i < n && (base + i == 0 || key[run_lds(i)] != key[run_lds(1 + i)])) {
             heads |= 1u << k;
             last_head = i;
         }
@@ -515,7 +546,7 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
         const bool head = (heads >> k) & 1u;
         if (head) run0 = base + i;
         if ((base + i - run0) % BWD_CHUNK == 0) starts |= 1u << k;
-        if (head && key[1 + i + BWD_CHUNK] == key[1 + i]) longs |= 1u << k;
+        if (head && key[run_lds(1 + i + BWD_CHUNK)] == key[run_lds(1 + i)]) longs |= 1u << k;
     }
     // three counts below 2^13 in one word
     static_assert(TILE <= 4096, "counts of a tile take 20 bits each");
@@ -577,7 +608,7 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
         const int i = tid * ITEMS + k;
         if (i >= n) continue;
         const bool head = (heads >> k) & 1u, lng = (longs >> k) & 1u;
-        const uint32_t kk = key[1 + i];
+        const uint32_t kk = key[run_lds(1 + i)];
         if (head) {
             b.ukeys[u] = kk;
             b.seg_chunk0[u] = c;
@@ -585,25 +616,34 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
             m += lng;
             ++u;
         }
-        seg[i] = (uint32_t)(u - 1);
+        seg[run_lds(i)] = (uint32_t)(u - 1);
         if ((starts >> k) & 1u) {
             int len = 1;  // of the chunk: the keys are sorted, so equal ends mean equal all through
 #pragma unroll
             for (int o = BWD_CHUNK / 2; o > 0; o >>= 1)
-                if (key[1 + i + len + o - 1] == kk) len += o;
+                if (key[run_lds(1 + i + len + o - 1)] == kk) len += o;
             const int32_t p0 = (int32_t)(base + i);
             b.chunk_desc[c++] = make_int4(p0, p0 + len, u - 1, head && !lng ? 1 : 2);
         }
     }
     __syncthreads();
+    uint32_t p[ITEMS];
+    int32_t bag[ITEMS];
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int i = k * NT + tid;
-        if (i >= n) continue;
-        const uint32_t p = pos[i];
-        if (p >= (uint64_t)nnz) continue;
-        b.sbag[base + i] = bag_of[p];
-        b.inv[p] = (int32_t)seg[i];
+        p[k] = pos[i < n ? i : 0];
+        p[k] = p[k] < (uint64_t)nnz ? p[k] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) bag[k] = bag_of[p[k]];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int i = k * NT + tid;
+        if (i < n) {
+            __builtin_nontemporal_store(bag[k], &b.sbag[base + i]);
+            b.inv[p[k]] = (int32_t)seg[run_lds(i)];
+        }
     }
 }
 
