@@ -164,7 +164,7 @@ typedef struct {
     int64_t evictions;          /* misses placed in a slot that held a row              */
     int64_t bytes_fill;         /* host -> HBM bytes of miss fills                      */
     int64_t bytes_writeback;    /* HBM -> host bytes of evicted rows                    */
-    int64_t hash_rebuilds;
+    int64_t hash_rebuilds;      /* of the Hit-Map's hash (0 where it is one entry per row) */
     int64_t chunks;             /* backward work chunks processed                       */
     int64_t min_capacity_margin;/* min over plans and tables of unheld slots - misses  */
     int64_t device_bytes;       /* device memory held by the context                    */
@@ -226,7 +226,7 @@ typedef struct {
 } sp_plan_dump;
 
 /*
- * Create a context: allocates Storage (sum(slots) x D fp32), the Hit-Map hash,
+ * Create a context: allocates Storage (sum(slots) x D fp32), the Hit-Map,
  * per-slot metadata and holds, two int32 per row of every table (sum(rows) x 8
  * bytes: the row index behind the holds of filled rows), the window ring and
  * staging buffers on config->device, and four library streams at default

@@ -3,10 +3,11 @@
 //
 // Streams.  The caller's stream runs forward and backward.  The library has
 // four: the ingest stream sorts and deduplicates window batches (and carries
-// large write-back copies), the plan stream runs the query and the commit
-// sequence, the move stream runs the miss fill (and, with the staged fill,
-// the host-to-device copies of gathered rows), and the copy stream carries
-// small device-to-host copies of evicted rows.  Host threads gather missing
+// large write-back copies of the staged fill, while the plan stream takes the
+// sorts), the plan stream runs the query and the commit sequence, the move
+// stream runs the miss fill (and, with the staged fill, the host-to-device
+// copies of gathered rows; with the mapped fill the evicted rows leave there
+// too), and the copy stream carries small copies of evicted rows.  Host threads gather missing
 // rows into pinned staging (staged fill) and scatter evicted rows into the
 // host tables ([Collect] / [Exchange] / [Insert] of Sec. IV-B, with the
 // CPU-side work done off the critical path).
@@ -344,8 +345,11 @@ constexpr int64_t ID_ALIGN = 64;
 static int64_t ids_at(int64_t nbags) { return (nbags + ID_ALIGN) / ID_ALIGN * ID_ALIGN; }
 
 // staging slots of evicted rows (fill of plan p, copy of plan p - 1 and the
-// host scatter of plan p - 2 can all be in flight)
-constexpr int MAX_NSTAGE = 3;
+// host scatter of plan p - 2 can all be in flight).  The mapped fill takes a
+// fourth where slots are small: its move needs the host side of the slot free
+// before it is enqueued, one plan earlier than a copy issued by the next plan.
+constexpr int MAX_NSTAGE = 4;
+constexpr int64_t FOUR_SLOTS_BYTES = 64ll << 20;
 // staged fill: bytes of gathered rows per host-to-device copy, an eighth of
 // the plan's rows within these bounds (measured on an MI355X beside a
 // device-to-host copy of the same size: 8 MiB copies reach 45 GB/s, 32 MiB
@@ -363,6 +367,8 @@ constexpr int64_t IDCOPY_GRAIN_BYTES = 2ll << 20;
 // writes them in about 10 us; 1.7k rows of 128 bytes took 13 us on two threads,
 // 27 us with eight woken for four pieces, and the step 71 and 79 us)
 constexpr int64_t SCATTER_PIECE_BYTES = 64 << 10;
+// sp_flush copies and scatters this much at a time
+constexpr int64_t FLUSH_PIECE_BYTES = 2 << 20;
 // write-back copies above this size go on the ingest stream, where they
 // overlap the next fill; smaller ones go on the copy stream
 constexpr int64_t SMALL_COPY_BYTES = 8ll << 20;
@@ -490,7 +496,7 @@ struct sp_ctx {
     // pinned staging (stage_dev is stage_hdev, its device-visible address), slot
     // fills % nstage; slot_ticket: the last plan whose rows are in the slot
     int64_t fills = 0;
-    int64_t slot_ticket[MAX_NSTAGE]{-1, -1, -1};
+    int64_t slot_ticket[MAX_NSTAGE]{-1, -1, -1, -1};
     int64_t last_job = -1;     // last plan handed to the write-back thread
     int64_t last_fill = -1;    // mapped fill: last plan with misses
     int64_t filled_upto = -1;  // mapped fill: fills of plans up to this one are known done
@@ -1082,7 +1088,8 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     TRY(dalloc(h, &h->sel_key, S));
     TRY(dalloc(h, &h->partial, nchunk_max * h->D));
     h->stage_rows = std::min<int64_t>(NM, S);
-    h->nstage = MAX_NSTAGE;
+    const int64_t slot_bytes = h->stage_rows * (h->D + 1) * (int64_t)sizeof(float);
+    h->nstage = !h->staged && slot_bytes <= FOUR_SLOTS_BYTES ? 4 : 3;
     for (int i = 0; i < h->nstage; ++i) {
         // (whole 16-byte words: the write-back copies such)
         TRY(palloc(h, &h->stage_host[i], h->stage_rows * (h->D + 1) + 4));
@@ -2181,25 +2188,35 @@ extern "C" sp_status sp_flush(sp_handle h)
     HIPCHK(h, hipDeviceSynchronize());
     TRY(join_jobs(h, h->last_job));
     h->deadlines.clear();
+    if (h->stage_rows == 0) return SP_OK;  // no batch may have an ID: nothing is ever cached
     std::vector<int32_t> keys((size_t)h->total_slots);
     HIPCHK(h, hipMemcpy(keys.data(), h->key_of_slot, sizeof(int32_t) * h->total_slots,
                         hipMemcpyDeviceToHost));
-    const int rb = h->tb.row_bits;
-    const uint32_t mask = (1u << rb) - 1u;
-    const size_t row_bytes = sizeof(float) * (size_t)h->D;
-    for (int64_t s0 = 0; s0 < h->total_slots; s0 += h->stage_rows) {
-        const int64_t cnt = std::min(h->stage_rows, h->total_slots - s0);
+    // In pieces through the pinned write-back staging (free: every job has been
+    // joined), the next piece's copy beside the scatter of this one, which the
+    // scatter threads share (the write-back thread is idle).  Four steps and a
+    // flush of 32k rows of 256 bytes: 1.23 ms with one copy and one thread
+    // after the other, 0.82 ms so.
+    const int64_t row_bytes = (int64_t)sizeof(float) * h->D;
+    const int64_t piece = std::max<int64_t>(1, std::min(h->stage_rows, FLUSH_PIECE_BYTES / row_bytes));
+    const int64_t np = (h->total_slots + piece - 1) / piece;
+    auto rows_of = [&](int64_t q) { return std::min(piece, h->total_slots - q * piece); };
+    auto fetch = [&](int64_t q) -> hipError_t {  // piece q into staging slot q % 2
+        const int64_t s0 = q * piece, n = rows_of(q);
         bool any = false;
-        for (int64_t i = 0; i < cnt && !any; ++i) any = keys[s0 + i] >= 0;
-        if (!any) continue;
-        HIPCHK(h, hipMemcpy(h->stage_host[0], h->storage + s0 * h->D, row_bytes * cnt,
-                            hipMemcpyDeviceToHost));
-        for (int64_t i = 0; i < cnt; ++i) {
-            const int32_t key = keys[s0 + i];
-            if (key < 0) continue;
-            memcpy(h->host[key >> rb] + (int64_t)(key & mask) * h->D, h->stage_host[0] + i * h->D,
-                   row_bytes);
-        }
+        for (int64_t i = 0; i < n && !any; ++i) any = keys[s0 + i] >= 0;
+        if (any) launch_push(h->storage + s0 * h->D, h->stage_hdev[q % 2], n * row_bytes, h->s_copy);
+        const hipError_t r = hipGetLastError();
+        return r != hipSuccess ? r : hipEventRecord(h->ev_d2h[q % 2], h->s_copy);
+    };
+    const int64_t grain = std::max<int64_t>(64, SCATTER_PIECE_BYTES / row_bytes);
+    HIPCHK(h, fetch(0));
+    for (int64_t q = 0; q < np; ++q) {
+        if (q + 1 < np) HIPCHK(h, fetch(q + 1));
+        HIPCHK(h, hipEventSynchronize(h->ev_d2h[q % 2]));
+        h->scatter.run(rows_of(q), grain, [&](int64_t b, int64_t e) {
+            copy_rows(h->host, h->tb, h->D, h->stage_host[q % 2], keys.data() + q * piece, b, e, true);
+        });
     }
     return SP_OK;
 }
