@@ -390,7 +390,11 @@ class ScratchPipe:
                 ids = np.ascontiguousarray(ids, dtype=np.int32)
                 off = np.ascontiguousarray(off, dtype=np.int32)
                 keep.append((ids, off))
-                arr[i] = self._describe(ids, off)
+                b = arr[i]  # a view of the entry (zeroed: on_device is 0)
+                b.batch = (off.shape[0] - 1) // self.T
+                b.nnz = ids.shape[0]
+                b.ids = ids.__array_interface__["data"][0] if ids.size else None
+                b.bag_off = off.__array_interface__["data"][0]
         return sp_plan(self.handle, arr, n)
 
     def forward(self, ticket: int, out, stream=None) -> None:
