@@ -1714,7 +1714,11 @@ static sp_status plan_fill(sp_ctx *h, int64_t k, int nhold, int pf_d, bool timin
         // fill, even where its queue is the move stream's
         TRY(issue_copy(h, h->s_copy));
         h->copy_pending = k;
-        h->copy_n = mj.n;
+        // Victims that were all never-used slots hold nothing to write back.
+        // (Copied all the same, 369 MB per step of 64 tables with room for
+        // every row shared the link with the fill and sent the sorts to the plan
+        // stream, ahead of the missing keys: 10.9 ms per step, 6.9 without.)
+        h->copy_n = h->last_fresh ? 0 : mj.n;
     } else {
         HIPCHK(h, enqueue_move(h, mj, nullptr));
         h->last_fill = k;
