@@ -254,8 +254,9 @@ sp_status sp_create(const sp_config *config, sp_handle *out);
  * plan issue the next plan's query right behind its own commit.  Batches
  * enter the device window
  * ring once, when first seen, and are not read again: the same batch must be
- * passed with the same content every time it appears (after a failed plan
- * all of that call's batches are read again on the next call).  Host window
+ * passed with the same content every time it appears (after a plan rejected
+ * for its IDs, offsets or capacity all of that call's batches are read again
+ * on the next call, and may have other content from then on).  Host window
  * buffers may be reused when the call returns; device ones once a call that
  * holds their batch has returned (a batch prepared ahead in device memory is
  * read asynchronously, before the query of the first plan that holds it).

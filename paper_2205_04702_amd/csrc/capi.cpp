@@ -403,6 +403,13 @@ struct sp_ctx {
     int32_t *lastq = nullptr, *pend = nullptr;  // per row: see RowIndex
     int32_t *hcnt = nullptr;     // [MAX_TABLES][HOLD_RING] slots per table and hold_to value
     int64_t entered = -1;        // last batch whose slots an accepted plan has marked held
+    // A rejected plan's window is read again, perhaps with other content, also
+    // the batches an earlier plan marked held: the next accepted plan drops
+    // every hold and enters its window anew (stale_holds).  lastq may name a
+    // batch up to stale_upto for rows it no longer has: plans up to that one
+    // search the window's keys instead.
+    bool stale_holds = false;
+    int64_t stale_upto = -1;
     // the last plan with misses took them all from never-used slots (so it
     // wrote nothing back)
     bool last_fresh = true;
@@ -1482,6 +1489,20 @@ static sp_status ingest_deferred(sp_ctx *h)
     return SP_OK;
 }
 
+// Plan k is rejected: the batches of this call's window are read again at the
+// next call.  Where an earlier plan marked some of them held, what was derived
+// from their old content no longer counts: their holds, the batches that lastq
+// names, and the write-back deadlines (a row that no batch of an earlier
+// window had may be in the new one, so every write-back is due at plan k).
+static void reread_window(sp_ctx *h, int64_t k, int n)
+{
+    for (int w = 0; w < n; ++w) h->ring_batch[(k + w) % h->nring] = -1;
+    if (k > h->entered) return;
+    h->stale_holds = true;
+    h->stale_upto = std::max(h->stale_upto, std::min(k + n - 1, h->entered));
+    for (auto &d : h->deadlines) d.second = std::min(d.second, k);
+}
+
 // RAW-4: a row evicted by plan p may be refilled from plan p + n_p on (n_p
 // batches in p's hold window; n_p - d with prefetch depth d, which fills the
 // batches after the planned one): before plan k reads the host tables for
@@ -1598,12 +1619,12 @@ static sp_status enqueue_query(sp_ctx *h, int64_t k, int nhold, uint32_t *seq_ou
                          h->pf_flag, h->max_ids};
     // rows: the planned batch, the successors to prefetch, and the batches
     // entering the hold window.  A batch marked held by an earlier plan but no
-    // longer in the window (the caller shortened it) makes every hold be
-    // rebuilt from this window and the past ones.
+    // longer in the window (the caller shortened it), or read again since,
+    // makes every hold be rebuilt from this window and the past ones.
     QueryRows &qr = th.qr;
     qr = QueryRows{};
     qr.span = h->L + h->P;
-    qr.rebuild = h->entered > k + nhold - 1;
+    qr.rebuild = h->stale_holds || h->entered > k + nhold - 1;
     int64_t max_nnz = 0;
     for (int w = 0; w < nwin; ++w) {
         qr.qoff[w] = w < nhold ? w : -(w - nhold + 1);
@@ -1809,7 +1830,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     double tE = host_ms();
     h->host_ms[2] += tE - tD;
     if (c.err & (ERR_ID_RANGE | ERR_OFFSETS | ERR_TABLE_IDS)) {
-        for (int w = 0; w < n; ++w) h->ring_batch[(k + w) % h->nring] = -1;  // re-read on retry
+        reread_window(h, k, n);
         return fail(h, SP_ERR_INVALID_ARG, "%s in the window",
                     (c.err & ERR_ID_RANGE)  ? "row ID out of range"
                     : (c.err & ERR_OFFSETS) ? "malformed bag offsets"
@@ -1835,7 +1856,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
         const int64_t need = (int64_t)c.miss[t] + pf_tot[t];
         margin = std::min<int64_t>(margin, free_slots - need);
         if (need > free_slots) {
-            for (int w = 0; w < n; ++w) h->ring_batch[(k + w) % h->nring] = -1;  // re-read on retry
+            reread_window(h, k, n);
             return fail(h, SP_ERR_CAPACITY,
                         "table %d: %lld misses (%d to prefetch) but only %lld unheld slots (plan %lld)",
                         t, (long long)need, pf_tot[t], (long long)free_slots, (long long)k);
@@ -1922,7 +1943,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     }
     const RowIndex ri{h->rbase, h->lastq, h->pend};
     // the filled rows' holds from lastq / pend when at most one batch enters
-    const bool fast_hold = !th.qr.rebuild && hr.n <= 1;
+    const bool fast_hold = !th.qr.rebuild && hr.n <= 1 && k > h->stale_upto;
     const int32_t ent = hr.n == 1 ? hr.q_off[0] : 0;
     if (th.qr.rebuild) {
         launch_hold_rebuild(h->tb, hr, ri, h->hold_to, h->hcnt, u, h->s_plan);
@@ -1995,6 +2016,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     launch_commit(h->tb, h->map, tk, n_miss, th.n_unique, h->key_of_slot, h->last_use, h->uses, u, pf_on, wk, hr, ri, h->hold_to, h->hcnt, h->cnt, h->s_plan);
     CHECK_LAUNCH(h);
     h->entered = th.qr.rebuild ? k + nhold - 1 : std::max(h->entered, k + nhold - 1);
+    h->stale_holds = false;
     if (h->ws_plan.overflow) return fail(h, SP_ERR_HIP, "internal: scan workspace too small");
     HIPCHK(h, hipStreamWriteValue64(h->s_plan, h->sem + SEM_PLANNED, (uint64_t)k + 1, 0));
     // the event only serves event-wait mode; value waits on SEM_PLANNED always work
