@@ -7,6 +7,7 @@ stream (torch.cuda.current_stream()) for forward/backward.
 """
 from __future__ import annotations
 
+import collections
 import ctypes as C
 import mmap
 import os
@@ -357,6 +358,7 @@ class ScratchPipe:
                         prefetch=self.prefetch, fill=FILLS[fill])
         self.handle = sp_create(cfg)
         self._desc_cache = {}
+        self._recent = collections.deque(maxlen=SP_MAX_AHEAD + 1)  # windows of the last plans
 
     def _describe(self, ids, off) -> sp_batch:
         B = (len(off) - 1) // self.T
@@ -374,18 +376,20 @@ class ScratchPipe:
         n = len(window)
         arr = (sp_batch * n)()
         keep = []
+        tensors = False
         for i, (ids, off) in enumerate(window):
-            if hasattr(ids, "data_ptr"):
-                # device tensors: descriptors cached per tensor pair (the cache
-                # holds the tensors, so their addresses stay valid)
-                key = (id(ids), id(off))
-                hit = self._desc_cache.get(key)
-                if hit is None:
+            ptr = getattr(ids, "data_ptr", None)
+            if ptr is not None:
+                # device tensors: a descriptor is made once per pair of addresses and
+                # sizes, which is all it says (a tensor may get another storage)
+                key = (ptr(), ids.nbytes, off.data_ptr(), off.nbytes)
+                d = self._desc_cache.get(key)
+                if d is None:
                     if len(self._desc_cache) >= 64:
                         self._desc_cache.pop(next(iter(self._desc_cache)))
-                    hit = (self._describe(ids, off), ids, off)
-                    self._desc_cache[key] = hit
-                arr[i] = hit[0]
+                    d = self._desc_cache[key] = self._describe(ids, off)
+                arr[i] = d
+                tensors = True
             else:
                 ids = np.ascontiguousarray(ids, dtype=np.int32)
                 off = np.ascontiguousarray(off, dtype=np.int32)
@@ -395,6 +399,8 @@ class ScratchPipe:
                 b.nnz = ids.shape[0]
                 b.ids = ids.__array_interface__["data"][0] if ids.size else None
                 b.bag_off = off.__array_interface__["data"][0]
+        if tensors:  # one handed over SP_MAX_AHEAD plans before one holds it is read meanwhile
+            self._recent.append(tuple(window))
         return sp_plan(self.handle, arr, n)
 
     def forward(self, ticket: int, out, stream=None) -> None:
@@ -426,6 +432,7 @@ class ScratchPipe:
         if getattr(self, "handle", None):
             sp_destroy(self.handle)
             self.handle = None
+            self._recent.clear()
 
     def __enter__(self):
         return self

@@ -181,3 +181,47 @@ def test_header_constants_match_the_binding():
             assert policies[name] == val, name
         elif name.startswith(("SP_FLAG_", "SP_ERR_")) or hasattr(sp, name):
             assert getattr(sp, name) == val, name
+
+
+def test_descriptors_follow_the_tensors_storage(monkeypatch):
+    """plan() describes a batch by what its tensors are now: another storage or another
+    length in the same tensor objects is seen.  It keeps the tensors of the last plans
+    (batches handed over early are read until a plan holds them) and no others."""
+    import collections
+    import gc
+    import weakref
+    import torch
+    seen = []
+    monkeypatch.setattr(sp, "sp_plan", lambda h, arr, n: seen.append(
+        [(b.batch, b.nnz, b.ids, b.bag_off) for b in arr[:n]]))
+    ctx = sp.ScratchPipe.__new__(sp.ScratchPipe)
+    ctx.T, ctx._desc_cache, ctx.handle = 2, {}, None
+    ctx._recent = collections.deque(maxlen=sp.SP_MAX_AHEAD + 1)
+
+    def described(ids, off):
+        ctx.plan([(ids, off)])
+        return seen[-1][0] == ((off.shape[0] - 1) // 2, ids.shape[0], ids.data_ptr() or None,
+                               off.data_ptr())
+
+    ids, off = torch.zeros(40, dtype=torch.int32), torch.zeros(9, dtype=torch.int32)
+    assert described(ids, off) and described(ids, off)
+    ids.data = torch.zeros(40, dtype=torch.int32)  # same length elsewhere
+    assert described(ids, off)
+    ids.resize_(24)  # shorter in the same place
+    assert described(ids, off)
+    off.set_(torch.zeros(17, dtype=torch.int32))
+    assert described(ids, off)
+    other = torch.zeros(24, dtype=torch.int32)  # another tensor beside the same offsets
+    assert described(other, off) and described(ids, off)
+    gone = weakref.ref(ids)
+    del ids
+    for _ in range(sp.SP_MAX_AHEAD):
+        described(other, off)
+        gc.collect()
+        assert gone() is not None
+    described(other, off)
+    gc.collect()
+    assert gone() is None
+    for n in range(100):  # the descriptors kept are few
+        described(torch.zeros(n + 1, dtype=torch.int32), off)
+    assert len(ctx._desc_cache) <= 64
