@@ -58,3 +58,39 @@ def test_sorts_ahead_of_small_and_large_writebacks(harness, batch, device_ids):
     r = harness.run_parity(w, fill="staged", device_ids=device_ids, prepare_ahead=2,
                            sync_each_step=False, check_fwd_steps=[0, 4, 6])
     assert r["stats"]["evictions"] > 3 * ids // 2
+
+
+@pytest.mark.parametrize("fill", ["mapped", "staged"])
+def test_flush_of_a_nearly_empty_scratchpad(harness, fill):
+    """Slots for a million rows, a few used: the pieces of the flush (8 slots, as the largest
+    batch has 8 IDs) that hold no row take no call of the runtime.  Such a call takes some
+    5 us, 125k of them over half a second; the bound leaves a scan of the keys 50 ms."""
+    import time
+    import numpy as np
+    import torch
+    rows, dim = 1_000_000, 16
+    host = sp.host_tables([rows], dim, fill)
+    host[0][:] = 1.0
+    ctx = sp.ScratchPipe([rows], dim, [rows], 0, host, 4, 8, fill=fill)
+    print(f"case sparse flush {fill}", flush=True)
+    try:
+        ids = np.array([5, 999_999, 7, 7, 123_456, 0, 31, 64], np.int32)
+        out = torch.zeros((4, dim), device="cuda:0")
+        grad = torch.ones((4, dim), device="cuda:0")
+        want = np.ones(rows, np.float32)
+        for step in range(3):
+            mine = (ids.astype(np.int64) + 1000 * step) % rows
+            t = ctx.plan([(mine.astype(np.int32), np.array([0, 2, 4, 6, 8], np.int32))])
+            ctx.forward(t, out)
+            ctx.backward_update(t, grad, 0.25)
+            np.subtract.at(want, mine, np.float32(0.25))
+        took = []
+        for _ in range(3):
+            t0 = time.perf_counter()
+            ctx.flush()
+            took.append(time.perf_counter() - t0)
+        assert np.array_equal(host[0], np.repeat(want, dim).reshape(rows, dim))
+        assert min(took) < 0.05, took
+    finally:
+        ctx.close()
+        host.close()
