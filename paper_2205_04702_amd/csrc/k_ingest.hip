@@ -3,6 +3,8 @@
 // equal keys that the backward pass coalesces (gradient duplication and
 // coalescing, Sec. II-B).  Everything here runs once per batch, when the batch
 // enters the look-forward window.
+#include <algorithm>
+
 #include "sp_device.h"
 #include "sp_internal.h"
 
@@ -36,8 +38,10 @@ void launch_zero_i32(int32_t *p, int64_t n, hipStream_t s) { launch_fill_i32(p, 
 // bag_of for them, each lane finding its position's bag among the 64 offsets
 // by a search over the lanes.  Stores are whole 256-byte lines; one thread per
 // bag writing its positions one by one took 0.24 ms alone (0.9 ms beside the
-// training kernels) for 21M IDs.
-__device__ __forceinline__ void mark_bags(int64_t first, const int32_t *bag_off,
+// training kernels) for 21M IDs.  Where few bags hold many IDs, `parts` waves
+// share the positions of the 64 bags (wave `part` takes every parts-th 64 of
+// them, wave 0 validates and copies): bag_parts.
+__device__ __forceinline__ void mark_bags(int64_t first, int part, int parts, const int32_t *bag_off,
                                           int32_t *bag_off_copy, int32_t B, int64_t nnz,
                                           int64_t nbags, int64_t max_table_ids, int32_t *bag_of,
                                           int32_t *err)
@@ -48,7 +52,7 @@ __device__ __forceinline__ void mark_bags(int64_t first, const int32_t *bag_off,
     const int64_t gc = in ? g : nbags - 1;
     int64_t lo = bag_off[gc], hi = bag_off[gc + 1];
     int32_t bad = 0;
-    if (in) {
+    if (in && part == 0) {
         if (bag_off_copy != bag_off) {
             bag_off_copy[g] = (int32_t)lo;
             if (g == nbags - 1) bag_off_copy[g + 1] = (int32_t)hi;
@@ -64,7 +68,7 @@ __device__ __forceinline__ void mark_bags(int64_t first, const int32_t *bag_off,
     if (!in) lo = hi;  // lanes past the last bag start where it ends
     const int32_t lo32 = (int32_t)lo;
     const int64_t p0 = __shfl(lo32, 0, WAVE), p1 = __shfl((int32_t)hi, WAVE - 1, WAVE);
-    for (int64_t base = p0; base < p1; base += WAVE) {
+    for (int64_t base = p0 + part * WAVE; base < p1; base += (int64_t)parts * WAVE) {
         const int32_t p = (int32_t)(base + lane);
         int k = 0;  // the last of the 64 bags that starts at or before p
 #pragma unroll
@@ -84,7 +88,22 @@ __global__ void __launch_bounds__(BLOCK) k_bags(const int32_t *bag_off, int32_t 
 {
     const int64_t first = ((int64_t)blockIdx.x * (BLOCK / WAVE) + wave_id()) * WAVE;
     if (first < nbags)
-        mark_bags(first, bag_off, bag_off_copy, B, nnz, nbags, max_table_ids, bag_of, err);
+        mark_bags(first, 0, 1, bag_off, bag_off_copy, B, nnz, nbags, max_table_ids, bag_of, err);
+}
+
+// Waves per 64 bags: a wave's walk is a chain of some 0.3 us per 64 positions,
+// so it is cut to about BAG_STEPS steps for bags of the mean length, unless the
+// waves fill the chip as it is.  An ingest of 64 bags of 2000 IDs takes 0.60 ms
+// with one wave for them, 0.066 cut to 32 steps, 0.060 to 8 and 0.060 to 2;
+// 4096 bags of 300 IDs 0.20, 0.126, 0.126 and 0.123; 106k bags of 40 IDs 0.317
+// each way.
+constexpr int64_t BAG_STEPS = 8, BAG_WAVES = 4096;
+static int bag_parts(int64_t nnz, int64_t nbags)
+{
+    const int64_t waves = (nbags + WAVE - 1) / WAVE;
+    const int64_t steps = (nnz + waves * WAVE - 1) / (waves * WAVE);
+    const int64_t parts = std::min((steps + BAG_STEPS - 1) / BAG_STEPS, (BAG_WAVES + waves - 1) / waves);
+    return (int)std::max<int64_t>(parts, 1);
 }
 
 // ---------------------------------------------------------------- general path: segmented sort
@@ -187,13 +206,14 @@ __device__ __forceinline__ void sort_entries(uint64_t (&e)[ITEMS], bool first, c
 }
 
 // NT * ITEMS entries per tile.  Blocks past `groups` of the first launch mark
-// the bags instead.
+// the bags instead, `parts` waves each 64.
 template <int NT, int ITEMS>
 __global__ void __launch_bounds__(NT) k_sort_hist(Tables tb, const int32_t *ids,
                                                   const int32_t *bag_off, int32_t *bag_off_copy,
                                                   int32_t B, int64_t nnz, int64_t nbags,
                                                   int64_t max_table_ids, int32_t *bag_of,
-                                                  int32_t groups, const uint64_t *in, int q,
+                                                  int32_t parts, int32_t groups,
+                                                  const uint64_t *in, int q,
                                                   int passes, int G, uint32_t *thist,
                                                   uint32_t *ghist, int32_t *err)
 {
@@ -204,10 +224,11 @@ __global__ void __launch_bounds__(NT) k_sort_hist(Tables tb, const int32_t *ids,
     __shared__ int32_t t_s;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= groups) {
-        const int64_t first =
-            ((int64_t)(blockIdx.x - groups) * (NT / WAVE) + wave_id()) * WAVE;
+        const int64_t u = (int64_t)(blockIdx.x - groups) * (NT / WAVE) + wave_id();
+        const int64_t first = u / parts * WAVE;
         if (first < nbags)
-            mark_bags(first, bag_off, bag_off_copy, B, nnz, nbags, max_table_ids, bag_of, err);
+            mark_bags(first, (int)(u % parts), parts, bag_off, bag_off_copy, B, nnz, nbags,
+                      max_table_ids, bag_of, err);
         return;
     }
     // consecutive groups (one table's) on one XCD, as in the scatter
@@ -1231,14 +1252,15 @@ static void launch_general(const Tables &tb, const BatchDev &b, const int32_t *i
     while (G < 32 && (int64_t)G * G * tb.T < flat && flat / G > 1024) G *= 2;
     const int64_t groups = flat / G + tb.T + 1;
     uint32_t *const thist = sw.hist, *const ghist = sw.hist + tiles * SORT_BINS;
-    const int64_t bag_blocks = (nbags + NT - 1) / NT;
+    const int parts = bag_parts(nnz, nbags);
+    const int64_t bag_blocks = ((nbags + WAVE - 1) / WAVE * parts + NT / WAVE - 1) / (NT / WAVE);
     for (int q = 0; q < passes; ++q) {
         const uint64_t *const in = sw.e[(passes - q) & 1];  // the last pass writes e[0]
         uint64_t *const out = sw.e[(passes - 1 - q) & 1];
         hipLaunchKernelGGL((k_sort_hist<NT, ITEMS>),
                            dim3((unsigned)(groups + (q == 0 ? bag_blocks : 0))), dim3(NT), 0, s, tb,
                            ids, bag_off, b.bag_off, B, nnz, nbags, max_table_ids, b.bag_of,
-                           (int32_t)groups, in, q, passes, G, thist, ghist, sw.err);
+                           parts, (int32_t)groups, in, q, passes, G, thist, ghist, sw.err);
         hipLaunchKernelGGL((k_sort_scatter<NT, ITEMS>), dim3((unsigned)tiles), dim3(NT), 0, s, tb,
                            ids, bag_off, B, nnz, in, out, q, passes, G, (const uint32_t *)thist,
                            (const uint32_t *)ghist);
