@@ -145,6 +145,7 @@ struct TicketHost {
     int32_t stamp = 0;    // the query's stamp
     bool keys_direct = false;  // the query wrote the missing keys to pinned host memory
     int64_t nnz = 0, n_unique = 0, n_chunks = 0, n_multi = 0, n_miss = 0;
+    bool long_bags = false;
     int64_t n_own = 0;  // misses of the planned batch itself (n_miss less prefetched rows)
     int64_t prior_fill = -1;  // mapped fill: the last earlier plan with misses
     bool ev_planned = false;  // the plan recorded ev_planned (event-wait mode at plan time)
@@ -1030,7 +1031,7 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         TRY(dalloc(h, &b.seg_chunk0, N + 1));
         TRY(dalloc(h, &b.chunk_desc, nchunk_max));
         TRY(dalloc(h, &b.multi, multi_capacity(N, h->chunk)));
-        TRY(dalloc(h, &b.scal, T + 3));
+        TRY(dalloc(h, &b.scal, 5));
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ring_ready[r], hipEventDisableTiming));
     }
     h->h_off.assign(h->nring, nullptr);
@@ -1871,6 +1872,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
     th.n_unique = c.n_unique;
     th.n_chunks = c.n_chunks;
     th.n_multi = c.n_multi;
+    th.long_bags = c.long_bags != 0;
     th.n_miss = n_miss;
     th.n_own = n_own;
     th.ring = r0;
@@ -2134,7 +2136,7 @@ extern "C" sp_status sp_forward(sp_handle h, int64_t ticket, float *d_out, void 
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if ((h->flags & SP_FLAG_TIMING) && nbags > 0) HIPCHK(h, h->t_fwd.take(&e0, &e1));
     launch_forward(h->storage, h->D, h->total_slots, h->ring[th.ring].inv, h->tk[e].slot_u, th.n_unique,
-                   h->ring[th.ring].bag_off, nbags, d_out, s, e0, e1);
+                   h->ring[th.ring].bag_off, nbags, th.nnz, th.long_bags, d_out, s, e0, e1);
     CHECK_LAUNCH(h);
     h->forwarded = ticket + 1;
     if (h->flags & SP_FLAG_DEBUG_SYNC) HIPCHK(h, hipDeviceSynchronize());

@@ -65,6 +65,9 @@ __device__ __forceinline__ void mark_bags(int64_t first, int part, int parts, co
     if (bad) atomicOr(err, bad);
     lo = lo < 0 ? 0 : (lo > nnz ? nnz : lo);
     hi = hi < 0 ? 0 : (hi > nnz ? nnz : hi);
+    if (part == 0 && __ballot(in && hi - lo > FWD_LONG) && lane == 0 &&
+        !(__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & BATCH_LONG_BAG))
+        atomicOr(err, BATCH_LONG_BAG);
     if (!in) lo = hi;  // lanes past the last bag start where it ends
     const int32_t lo32 = (int32_t)lo;
     const int64_t p0 = __shfl(lo32, 0, WAVE), p1 = __shfl((int32_t)hi, WAVE - 1, WAVE);
@@ -612,8 +615,10 @@ __global__ void __launch_bounds__(NT) k_runs(const uint64_t *e, const int32_t *b
             const int32_t U = (int32_t)(uint32_t)tot_uc, C = (int32_t)(tot_uc >> 32);
             b.scal[0] = U;
             b.scal[1] = C;
-            b.scal[2] = atomicExch(err, 0);
+            const int32_t found = atomicExch(err, 0);
+            b.scal[2] = found & ~BATCH_LONG_BAG;
             b.scal[3] = (int32_t)tot_m;
+            b.scal[4] = (found & BATCH_LONG_BAG) != 0;
             b.seg_chunk0[U] = C;
             __hip_atomic_store(arrived, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -1015,6 +1020,7 @@ __global__ void __launch_bounds__(IG_THREADS) k_ingest_table(Tables tb, const in
         }
         if (lo > hi || lo < 0 || hi > nnz || (g == 0 && lo != 0) || (g == nbags - 1 && hi != nnz))
             err |= ERR_OFFSETS;
+        if (hi - lo > FWD_LONG) err |= BATCH_LONG_BAG;
         const int64_t a = lo - j0 < 0 ? 0 : lo - j0, e = hi - j0 > n ? n : hi - j0;
         for (int64_t i = a; i < e; ++i) bag_at[i] = (uint32_t)lb;
     }
@@ -1214,8 +1220,10 @@ __global__ void __launch_bounds__(IG_THREADS) k_ingest_table(Tables tb, const in
         if ((int64_t)U < cap_u + 1) b.seg_chunk0[U] = (int32_t)(C0 + nC);
         b.scal[0] = (int32_t)U;
         b.scal[1] = (int32_t)(C0 + nC);
-        b.scal[2] = (int32_t)(before_s[3] | (uint32_t)err_s);
+        const int32_t found = (int32_t)(before_s[3] | (uint32_t)err_s);
+        b.scal[2] = found & ~BATCH_LONG_BAG;
         b.scal[3] = (int32_t)(M0 + nM);
+        b.scal[4] = (found & BATCH_LONG_BAG) != 0;
     }
 }
 
@@ -1307,7 +1315,7 @@ void launch_ingest(const Tables &tb, const BatchDev &b, const int32_t *ids, cons
         return;
     }
     if (nnz == 0) {  // only the offsets to validate and copy
-        launch_zero_i32(b.scal, 4, s);
+        launch_zero_i32(b.scal, 5, s);
         if (nbags > 0)
             hipLaunchKernelGGL(k_bags, dim3((unsigned)((nbags + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0,
                                s, bag_off, b.bag_off, B, nnz, nbags, max_table_ids, b.bag_of,

@@ -138,6 +138,7 @@ __global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T, Hi
         seen |= atomicExch(&cnt->n_unique, scal0[0]) == INT32_MIN;
         seen |= atomicExch(&cnt->n_chunks, scal0[1]) == INT32_MIN;
         seen |= atomicExch(&cnt->n_multi, scal0[3]) == INT32_MIN;
+        seen |= atomicExch(&cnt->long_bags, scal0[4]) == INT32_MIN;
     }
     const uint32_t *const ukw = pick_uniform(pa.uk, w);
     int32_t *const esw = pick_uniform(qr.eslot, w);

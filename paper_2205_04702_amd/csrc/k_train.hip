@@ -5,6 +5,8 @@
 // pass with fully coalesced 16-byte loads.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "sp_device.h"
 #include "sp_internal.h"
 
@@ -61,76 +63,64 @@ __device__ __forceinline__ float4 reduce_rows(float4 acc)
 // of positions, hidden behind the other waves, and spares the plan a pass that
 // writes a slot per position (it was most of a large commit).
 //
-// One group of GW lanes per bag: as many as a row has words, eight at least
-// (then several rows at a time).  A bag is a chain of dependent loads (offsets,
-// unique keys, slots, rows), which is what bounds this kernel where the rows
-// come from L2, so the more bags a wave works on at once the better: with one
-// wave per bag, 53k bags of four rows of 64 floats took 19 us, 12 now; 53k bags
-// of one row of 16 floats 18 us, 7 now.  Large batches of long bags are bound
-// by their rows instead: 524k bags of 40 rows of 64 floats 0.43 ms, 0.40 now
-// (13.7 TB/s of requests); 106k bags of 40 rows of 128 floats 0.195 ms as
-// before (11.2 TB/s of requests, a quarter of them distinct rows).  The group reads IB positions' slots at a time (the next ones while this block's
-// rows arrive) and broadcasts them by shuffles, FWD_ROWS row loads in flight
-// per lane.  Sums run over FWD_ACC partial sums in position order.
+// A group of GW lanes adds one bag.  A bag is a chain of dependent loads
+// (offsets, unique keys, slots, rows), which is what bounds this kernel where the
+// rows come from L2.  With many bags, a group is as many lanes as a row has
+// words, eight at least (then several rows at a time), so that a wave works on
+// several bags at once: with one wave per bag, 53k bags of four rows of 64 floats
+// took 19 us, 12 so; 53k bags of one row of 16 floats 18 us, 7 so.  Large batches
+// of long bags are bound by their rows either way: 524k bags of 40 rows of 64
+// floats 0.43 ms and 0.40 (13.7 TB/s of requests); 106k bags of 40 rows of 128
+// floats 0.195 ms (11.2 TB/s of requests, a quarter of them distinct rows).
+// With few or long bags a group is a whole wave (fwd_whole_wave), and where a
+// batch has single bags above FWD_LONG positions among shorter ones (SKEW) the
+// waves of a block share these, a whole wave for each.
 constexpr int FWD_ROWS = 8;
 constexpr int FWD_ACC = 4;
 constexpr int fwd_lanes(int lpr) { return lpr < 8 ? 8 : lpr; }
 
-template <int LPR>
-__global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ storage,
-                                                   const int32_t *__restrict__ inv,
-                                                   const int32_t *__restrict__ slot_u,
-                                                   int64_t n_unique,
-                                                   const int32_t *__restrict__ bag_off,
-                                                   int64_t nbags, int64_t nslots,
-                                                   float4 *__restrict__ out)
+// The sum of the rows of one bag per group of GW lanes, in every lane of the
+// group with that word: positions beg .. beg + len; all groups of the wave walk
+// as far as its longest (in 32 bits: fewer registers, more waves).  The group reads IB positions' slots at a time (the
+// next ones while this block's rows arrive) and broadcasts them by shuffles,
+// FWD_ROWS row loads in flight per lane.  Sums run over FWD_ACC partial sums
+// in position order.
+template <int LPR, int GW>
+__device__ __forceinline__ float4 bag_sum(const float4 *__restrict__ storage,
+                                          const int32_t *__restrict__ inv,
+                                          const int32_t *__restrict__ slot_u, int64_t n_unique,
+                                          int64_t nslots, int64_t beg, int32_t len, int32_t longest)
 {
-    constexpr int GW = fwd_lanes(LPR);
     constexpr int RPG = GW / LPR;                     // rows per load of a group
     constexpr int BATCH = RPG * FWD_ROWS;             // positions per batch of loads
     constexpr int IPL = BATCH > GW ? BATCH / GW : 1;  // positions held per lane
     constexpr int IB = IPL * GW;                      // positions per block
-    // consecutive bags (one table's) on one XCD: the table's hot rows share its L2
-    const int64_t g = (xcd_block(blockIdx.x, gridDim.x) * BLOCK + threadIdx.x) / GW;
     const int lane = lane_id(), gl = lane % GW, g0 = lane - gl;
     const int sub = gl / LPR, c = gl % LPR;
-    int64_t beg = 0, end = 0;
-    if (g < nbags) {
-        beg = bag_off[g];
-        end = bag_off[g + 1];
-    }
-    const int64_t len = end - beg > 0 ? end - beg : 0;
-    // the wave's longest bag: all groups walk as far
-    int64_t longest = len;
-#pragma unroll
-    for (int o = GW; o < WAVE; o <<= 1) {
-        const int64_t x = __shfl_xor((int32_t)longest, o, WAVE);
-        longest = x > longest ? x : longest;
-    }
     float4 acc[FWD_ACC];
 #pragma unroll
     for (int k = 0; k < FWD_ACC; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     int32_t ui[IPL], slot[IPL];
-    auto load_unique = [&](int64_t base) {  // lane gl holds positions base + l * GW + gl
+    auto load_unique = [&](int32_t base) {  // lane gl holds positions base + l * GW + gl
 #pragma unroll
         for (int l = 0; l < IPL; ++l) {
-            const int64_t k = base + l * GW + gl;
+            const int32_t k = base + l * GW + gl;
             ui[l] = k < len ? inv[beg + k] : 0;
         }
     };
-    auto load_slots = [&](int64_t base) {
+    auto load_slots = [&](int32_t base) {
 #pragma unroll
         for (int l = 0; l < IPL; ++l) {
-            const int64_t k = base + l * GW + gl;
+            const int32_t k = base + l * GW + gl;
             const int32_t r = k < len ? slot_u[(uint32_t)ui[l] < (uint64_t)n_unique ? ui[l] : 0] : 0;
             slot[l] = (uint32_t)r < (uint64_t)nslots ? r : 0;  // never leave the array
         }
     };
     load_unique(0);
     load_slots(0);
-    for (int64_t base = 0; base < longest; base += IB) {
-        const int n = (int)(len - base < IB ? (len - base < 0 ? 0 : len - base) : IB);
-        const int most = (int)(longest - base < IB ? longest - base : IB);
+    for (int32_t base = 0; base < longest; base += IB) {
+        const int n = len - base < IB ? (len - base < 0 ? 0 : len - base) : IB;
+        const int most = longest - base < IB ? longest - base : IB;
         int32_t cur[IPL];
 #pragma unroll
         for (int l = 0; l < IPL; ++l) cur[l] = slot[l];
@@ -161,7 +151,134 @@ __global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ st
         for (int k = 0; k < FWD_ACC; k += 2 * o) acc[k] = f4_add(acc[k], acc[k + o]);
 #pragma unroll
     for (int o = LPR; o < GW; o <<= 1) acc[0] = f4_add(acc[0], f4_xor(acc[0], o));
-    if (g < nbags && sub == 0) out[g * LPR + c] = acc[0];
+    return acc[0];
+}
+
+// The sum of one bag's rows by a whole wave, in few registers: it is the rare
+// part of a kernel whose other part they bound.
+template <int LPR>
+__device__ __forceinline__ float4 long_sum(const float4 *__restrict__ storage,
+                                           const int32_t *__restrict__ inv,
+                                           const int32_t *__restrict__ slot_u, int64_t n_unique,
+                                           int64_t nslots, int64_t beg, int64_t end)
+{
+    constexpr int RPW = WAVE / LPR;  // rows per load
+    constexpr int ROWS = RPW * FWD_ROWS < WAVE ? FWD_ROWS : WAVE / RPW;
+    const int lane = lane_id(), sub = lane / LPR, c = lane % LPR;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto slot_at = [&](int64_t k) {
+        const int32_t u = inv[k < end ? k : end - 1];
+        const int32_t r = slot_u[(uint32_t)u < (uint64_t)n_unique ? u : 0];
+        return (uint32_t)r < (uint64_t)nslots ? r : 0;  // never leave the array
+    };
+    int32_t next = slot_at(beg + lane);
+    for (int64_t base = beg; base < end; base += WAVE) {
+        const int32_t cur = next;
+        const int n = (int)(end - base < WAVE ? end - base : WAVE);
+        next = slot_at(base + WAVE + lane);
+        for (int k0 = 0; k0 < n; k0 += RPW * ROWS) {
+            float4 v[ROWS];
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q) {
+                const int k = k0 + q * RPW + sub;
+                const int32_t r = __shfl(cur, k % WAVE, WAVE);
+                v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (k < n) v[q] = storage[(int64_t)r * LPR + c];
+            }
+#pragma unroll
+            for (int q = 0; q < ROWS; ++q) acc = f4_add(acc, v[q]);
+        }
+    }
+    return reduce_rows<LPR>(acc);
+}
+
+// SKEW: for batches with bags above FWD_LONG positions.  A block whose long bags
+// are few enough leaves them out of its groups' walk and its waves then take them
+// in turn.  It decides by the rows that the longest chain adds one after another,
+// in rows of one group, a bag's start (offsets, unique key, slot) being worth
+// three batches of loads.  53k bags, one in 200 of them of 1000 positions: rows of
+// 16 floats 95 us without, 26 so, 38 with a wave per bag; 128 floats 129, 82 and 91.
+// The barrier costs short bags 10 to 25% (53k bags of one row of 64 floats 7.7
+// us, 8.5 so), so batches without such bags go without.
+template <int LPR, int GW, bool SKEW>
+__global__ void __launch_bounds__(BLOCK) k_forward(const float4 *__restrict__ storage,
+                                                   const int32_t *__restrict__ inv,
+                                                   const int32_t *__restrict__ slot_u,
+                                                   int64_t n_unique,
+                                                   const int32_t *__restrict__ bag_off,
+                                                   int64_t nbags, int64_t nslots,
+                                                   float4 *__restrict__ out)
+{
+    constexpr int WAVES = BLOCK / WAVE, NG = WAVE / GW;
+    // consecutive bags (one table's) on one XCD: the table's hot rows share its L2
+    const int64_t first = xcd_block(blockIdx.x, gridDim.x) * (BLOCK / GW);
+    const int64_t g = first + threadIdx.x / GW;
+    const int lane = lane_id(), gl = lane % GW;
+    int64_t beg = 0, end = 0;
+    if (g < nbags) {
+        beg = bag_off[g];
+        end = bag_off[g + 1];
+    }
+    int32_t len = end - beg > 0 ? (int32_t)(end - beg) : 0;
+    // the wave's longest bag
+    int32_t longest = len;
+#pragma unroll
+    for (int o = GW; o < WAVE; o <<= 1) {
+        const int32_t x = __shfl_xor(longest, o, WAVE);
+        longest = x > longest ? x : longest;
+    }
+    if constexpr (!SKEW) {
+        const float4 x = bag_sum<LPR, GW>(storage, inv, slot_u, n_unique, nslots, beg, len, longest);
+        if (g < nbags && gl < LPR) out[g * LPR + gl] = x;
+    } else {
+        __shared__ int32_t n_s[WAVES], total_s[WAVES], longest_s[WAVES];
+        __shared__ int32_t bag_s[WAVES][NG];  // the long bags of each wave, in the block
+        const int w = wave_id();
+        const bool lng = len > FWD_LONG;
+        const uint64_t heads = __ballot(lng && gl == 0);
+        if (lane == 0) n_s[w] = __popcll(heads);
+        if (heads) {  // uniform over the wave
+            const int32_t t = wave_sum(lng && gl == 0 ? len : 0);
+            if (lane == 0) {
+                total_s[w] = t;
+                longest_s[w] = longest;
+            }
+            if (lng && gl == 0) bag_s[w][__popcll(heads & lanemask_lt())] = threadIdx.x / GW;
+        }
+        __syncthreads();
+        int n_long = 0;
+        int64_t total = 0, most = 0;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) {
+            const int c = n_s[k];
+            n_long += c;
+            if (c) {
+                total += total_s[k];
+                most = longest_s[k] > most ? longest_s[k] : most;
+            }
+        }
+        bool apart = false;  // uniform over the block
+        if (n_long) {
+            constexpr int START = 3 * FWD_ROWS * GW / LPR;
+            const int64_t share = total / WAVES > most ? total / WAVES : most;
+            apart = share / NG + START * ((n_long + WAVES - 1) / WAVES) < most;
+        }
+        if (apart) {
+            len = lng ? 0 : len;
+            longest = longest > FWD_LONG ? FWD_LONG : longest;
+        }
+        const float4 x = bag_sum<LPR, GW>(storage, inv, slot_u, n_unique, nslots, beg, len, longest);
+        if (g < nbags && !(apart && lng) && gl < LPR) out[g * LPR + gl] = x;
+        if (!apart) return;
+        for (int i = w; i < n_long; i += WAVES) {
+            int k = 0, j = i;
+            while (j >= n_s[k]) j -= n_s[k++];
+            const int64_t h = first + bag_s[k][j];
+            const float4 y =
+                long_sum<LPR>(storage, inv, slot_u, n_unique, nslots, bag_off[h], bag_off[h + 1]);
+            if (lane < LPR) out[h * LPR + lane] = y;
+        }
+    }
 }
 
 // ---------------------------------------------------------------- backward + SGD
@@ -577,14 +694,55 @@ void launch_move(float *storage, int dim, const Tables &tb, float *const *host_d
     default: hipExtLaunchKernelGGL(KERNEL<64>, GRID, dim3(BLOCK), 0, s, E0, E1, 0, __VA_ARGS__); break; \
     }
 
+// Whether a whole wave takes each bag: with few bags, of which groups of lanes
+// would leave most of the chip idle, unless they are a few rows each; and with
+// bags long enough that a wave's start does not show.  In us, groups and whole
+// waves, rows of 16 / 64 floats:
+//   2048 bags of   4   3.5 3.7 /  3.5 3.6     4096 bags of  10   3.7 4.0 /  4.1 3.9
+//   2048 bags of  40   5.4 3.8 /  7.9 4.8     4096 bags of  20   4.4 4.0 /  5.9 4.5
+//    512 bags of 300    31 6.9 /   41  13     4096 bags of 100    15  10 /   19  18
+//   8192 bags of  20   5.4 6.4 /  8.6 9.4     8192 bags of  40   9.1 9.4 /   14  15
+//   8192 bags of 300    47  43 /   92  89    32768 bags of 100    58  54 /  122 116
+//  16384 bags of  40    15  15 /   26  26    32768 bags of  20    15  19 /   26  27
+constexpr int64_t FWD_FEW_BAGS = 4096, FWD_FEW_MEAN = 16, FWD_MEAN = 100;
+static bool fwd_whole_wave(int64_t nbags, int64_t nnz)
+{
+    return nnz >= FWD_MEAN * nbags || (nbags <= FWD_FEW_BAGS && nnz >= FWD_FEW_MEAN * nbags);
+}
+
+template <int LPR, int GW, bool SKEW>
+static void forward_launch(const float4 *storage, int64_t nslots, const int32_t *inv,
+                           const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off,
+                           int64_t nbags, float4 *out, hipStream_t s, hipEvent_t e0, hipEvent_t e1)
+{
+    hipExtLaunchKernelGGL((k_forward<LPR, GW, SKEW>), grid_rows(nbags, GW), dim3(BLOCK), 0, s, e0,
+                          e1, 0, storage, inv, slot_u, n_unique, bag_off, nbags, nslots, out);
+}
+
 void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *inv,
-                    const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
-                    hipEvent_t e0, hipEvent_t e1)
+                    const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags,
+                    int64_t nnz, bool long_bags, float *out, hipStream_t s, hipEvent_t e0,
+                    hipEvent_t e1)
 {
     if (nbags <= 0) return;
-    SP_DISPATCH_LPR_EV(dim / 4, k_forward, grid_rows(nbags, fwd_lanes(dim / 4)), e0, e1,
-                       (const float4 *)storage,
-                       inv, slot_u, n_unique, bag_off, nbags, nslots, (float4 *)out);
+    const bool wave = fwd_whole_wave(nbags, nnz);
+    auto launch = [&](auto lpr) {
+        constexpr int LPR = decltype(lpr)::value, GW = fwd_lanes(LPR);
+        auto *f = wave          ? forward_launch<LPR, WAVE, false>
+                  : long_bags   ? forward_launch<LPR, GW, (GW < WAVE)>
+                                : forward_launch<LPR, GW, false>;
+        f((const float4 *)storage, nslots, inv, slot_u, n_unique, bag_off, nbags, (float4 *)out, s,
+          e0, e1);
+    };
+    switch (dim / 4) {
+    case 1: launch(std::integral_constant<int, 1>()); break;
+    case 2: launch(std::integral_constant<int, 2>()); break;
+    case 4: launch(std::integral_constant<int, 4>()); break;
+    case 8: launch(std::integral_constant<int, 8>()); break;
+    case 16: launch(std::integral_constant<int, 16>()); break;
+    case 32: launch(std::integral_constant<int, 32>()); break;
+    default: launch(std::integral_constant<int, 64>()); break;
+    }
 }
 
 void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,

@@ -61,11 +61,12 @@ struct DevCounters {
     int32_t n_unique;            // unique keys of the planned batch
     int32_t n_chunks;            // backward work chunks of the planned batch
     int32_t n_multi;             // its runs longer than one chunk
+    int32_t long_bags;           // it has bags of more than FWD_LONG IDs
     int32_t miss[MAX_TABLES];
     int32_t held[MAX_TABLES];
     int32_t pf[MAX_PF][MAX_TABLES];  // rows of successor w + 1 to prefetch (prefetch mode)
     int32_t err_sticky;          // ERR_HASH_FULL / ERR_PLAN from any earlier commit
-    int32_t pad2[3];
+    int32_t pad2[2];
 };
 constexpr int COUNTERS_CLEARED = (int)(offsetof(DevCounters, err_sticky) / sizeof(int32_t));
 constexpr int PART_COPIES = 16;  // copies of the per-table counters the probe adds into, at most
@@ -74,6 +75,9 @@ constexpr int PART_WORDS = (2 + MAX_PF) * MAX_TABLES;
 constexpr int COUNTER_WORDS = (int)(sizeof(DevCounters) / sizeof(int32_t));
 constexpr int32_t ERR_ID_RANGE = 1, ERR_OFFSETS = 2, ERR_HASH_FULL = 4, ERR_PLAN = 8;
 constexpr int32_t ERR_TABLE_IDS = 16;  // a table has more IDs than the configured bound
+// Not an error, but an ingest gathers it with them: a bag of more than FWD_LONG IDs.
+constexpr int32_t BATCH_LONG_BAG = 32;
+constexpr int32_t FWD_LONG = 128;
 
 // Entries of a batch's list of runs longer than one chunk: such a run has at
 // least chunk + 1 positions.
@@ -101,7 +105,8 @@ struct BatchDev {
     int4 *chunk_desc;                // [n_chunks] first pos, end pos, run, above 1 when the run
                                      // has more chunks
     int32_t *multi;                  // [n_multi] runs longer than one chunk (any order)
-    int32_t *scal;                   // [0] n_unique, [1] n_chunks, [2] ERR_* bits, [3] n_multi
+    int32_t *scal;                   // [0] n_unique, [1] n_chunks, [2] ERR_* bits, [3] n_multi,
+                                     // [4] whether it has a bag of more than FWD_LONG IDs
     int32_t *eslot;                  // [n_unique] slot of each unique key when the batch
                                      // entered the hold window (-1: not cached)
 };
@@ -245,8 +250,8 @@ struct IngestCons {
 };
 // Workspace of the general ingest path (one per stream that runs it): two
 // buffers of entries, digit counts, and the runs' tile counts and prefixes.
-// err gathers the batch's error bits and arrived the finished blocks; both are
-// zero between ingests.
+// err gathers the batch's error bits (and BATCH_LONG_BAG) and arrived the
+// finished blocks; both are zero between ingests.
 struct SortWs {
     uint64_t *e[2];
     uint32_t *hist;
@@ -363,9 +368,11 @@ void launch_move(float *storage, int dim, const Tables &tb, float *const *host_d
 // Copies bytes (rounded up to whole 16-byte words; both ends 16-byte aligned)
 // from device memory to pinned host memory (its device-visible address).
 void launch_push(const void *src, void *dst, int64_t bytes, hipStream_t s);
+// long_bags: the batch has bags of more than FWD_LONG of its nnz IDs.
 void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t *inv,
-                    const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags, float *out, hipStream_t s,
-                    hipEvent_t e0, hipEvent_t e1);
+                    const int32_t *slot_u, int64_t n_unique, const int32_t *bag_off, int64_t nbags,
+                    int64_t nnz, bool long_bags, float *out, hipStream_t s, hipEvent_t e0,
+                    hipEvent_t e1);
 // The fixed partial-sum array of sp_backward_update_static: its bytes, and
 // its device address on the current device.
 constexpr int64_t STATIC_PARTIAL_BYTES = 32ll << 20;
