@@ -170,7 +170,6 @@ struct MoveJob {
     bool gather = false;   // the staged fill's gather and copies, else the move itself
     int64_t k = 0, n = 0;  // plan, rows to place
     int sl = 0, e = 0;     // staging slot, ticket entry
-    int32_t u = 0;
     bool timing = false;
     int nwait = 0;
     Wait wait[MAX_WINDOW + 8];
@@ -386,7 +385,7 @@ struct sp_ctx {
     uint32_t flags = 0;
     int32_t max_batch = 0;
     int64_t max_ids = 0, max_table_ids = 0, nchunk_max = 0;
-    int key_bits = 0, chunk = 0;
+    int chunk = 0;
     Tables tb{};
     int64_t slots[MAX_TABLES]{}, total_slots = 0, maxS = 0;
     // per table: slots fresh[t] .. slots[t] - 1 have never held a row
@@ -462,8 +461,8 @@ struct sp_ctx {
     int spec_nhold = 0;
     hipStream_t last_update_stream = nullptr;
 
-    // scratch of the plan stream and of the ingest stream
-    uint32_t *tmp_k = nullptr, *tmp_v = nullptr, *hist = nullptr;
+    // scratch of the plan stream and of the ingests
+    uint32_t *hist = nullptr;  // digit counts of the victims' sort
     ScanWs ws_plan;
     SortWs ws_sort{};
     ScanWs ws_ingest;
@@ -762,7 +761,7 @@ static hipError_t enqueue_move(sp_ctx *h, const MoveJob &j, const float *staged)
     if (r != hipSuccess) return r;
     if (j.n > 0) {
         if (j.timing && (r = h->t_fill.begin(s)) != hipSuccess) return r;  // the kernel itself
-        launch_move(h->storage, h->D, h->tb, h->host_dev, h->tk[j.e], j.n, j.u, h->stage_dev[j.sl],
+        launch_move(h->storage, h->D, h->tb, h->host_dev, h->tk[j.e], j.n, h->stage_dev[j.sl],
                     staged, s);
         if ((r = hipGetLastError()) != hipSuccess) return r;
         if (j.timing && (r = h->t_fill.end(s)) != hipSuccess) return r;
@@ -950,8 +949,8 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     }
     h->total_slots = h->tb.slot_base[T];
     h->tb.row_bits = std::max(1, bits_for((uint64_t)(max_rows - 1)));
-    h->key_bits = bits_for((uint64_t)(T - 1)) + h->tb.row_bits;
-    if (h->key_bits > 31) return fail(nullptr, SP_ERR_INVALID_ARG, "tables x rows need %d key bits (max 31)", h->key_bits);
+    const int key_bits = bits_for((uint64_t)(T - 1)) + h->tb.row_bits;
+    if (key_bits > 31) return fail(nullptr, SP_ERR_INVALID_ARG, "tables x rows need %d key bits (max 31)", key_bits);
 
     h->staged = c->fill == SP_FILL_STAGED;
     h->poison = (c->flags & SP_FLAG_POISON) != 0;
@@ -1054,8 +1053,6 @@ static sp_status build(sp_ctx *h, const sp_config *c)
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ev_filled[k], hipEventDisableTiming));
         HIPCHK(nullptr, hipEventCreateWithFlags(&h->ev_upd[k], hipEventDisableTiming));
     }
-    TRY(dalloc(h, &h->tmp_k, N));
-    TRY(dalloc(h, &h->tmp_v, N));
     TRY(dalloc(h, &h->vk0, NM));
     TRY(dalloc(h, &h->vv0, NM));
     TRY(dalloc(h, &h->vk1, NM));
@@ -1078,15 +1075,14 @@ static sp_status build(sp_ctx *h, const sp_config *c)
     TRY(dalloc(h, &h->cnt, 1));
     TRY(dalloc(h, &h->cnt_part, (int64_t)PART_COPIES * PART_WORDS + 1));
     {
-        // scans: victims (tables x slots per table), misses and batches (N),
-        // radix histogram tables (at most N + 2048 entries)
-        // (and the query's tiles of unique keys, and the LDS ingest's workgroups)
-        const int64_t tiles = std::max({scan_tiles(T, h->maxS), scan_tiles(1, NM + 4096),
-                                        (N + QUERY_TILE - 1) / QUERY_TILE,
-                                        (int64_t)T * ingest_splits(T)}) + 2;
+        // plan stream: scans of victims (tables x slots per table), misses (NM)
+        // and radix histogram tables (at most NM + 2048 entries), and the
+        // query's tiles of unique keys; ingest: the LDS ingest's workgroups
+        h->ws_plan.max_tiles = std::max({scan_tiles(T, h->maxS), scan_tiles(1, NM + 4096),
+                                         (N + QUERY_TILE - 1) / QUERY_TILE}) + 2;
+        h->ws_ingest.max_tiles = (int64_t)T * ingest_splits(T);
         for (ScanWs *ws : {&h->ws_plan, &h->ws_ingest}) {
-            ws->max_tiles = tiles;
-            TRY(dalloc(h, &ws->status, LB_WORDS * tiles));
+            TRY(dalloc(h, &ws->status, LB_WORDS * ws->max_tiles));
             TRY(dalloc(h, &ws->counter, 1));
             ws->err = &h->cnt->err_sticky;
         }
@@ -1684,7 +1680,6 @@ static sp_status plan_fill(sp_ctx *h, int64_t k, int nhold, int pf_d, bool timin
     mj.n = th.n_miss;
     mj.sl = sl;
     mj.e = e;
-    mj.u = (int32_t)k;
     mj.timing = timing;
     // the device staging slot is free once plan k - nstage's copy has run
     // (issued two plans ago)
@@ -2171,7 +2166,7 @@ static sp_status backward_update(sp_handle h, int64_t ticket, const float *d_gra
     if ((h->flags & SP_FLAG_TIMING) && th.n_chunks > 0 && th.n_multi > 0)
         HIPCHK(h, h->t_cmb.take(&ev[2], &ev[3]));
     launch_backward(h->storage, h->D, h->total_slots, h->ring[th.ring], h->tk[e].slot_u,
-                    th.n_chunks, th.n_multi, h->chunk, d_grad, (int64_t)h->T * th.B, lr,
+                    th.n_chunks, th.n_multi, d_grad, (int64_t)h->T * th.B, lr,
                     partial, s, ev);
     CHECK_LAUNCH(h);
     HIPCHK(h, hipEventRecord(h->ev_upd[e], s));  // also frees ring entry e of the window

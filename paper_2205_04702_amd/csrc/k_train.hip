@@ -668,7 +668,7 @@ static dim3 grid_waves(int64_t n)
 }
 
 void launch_move(float *storage, int dim, const Tables &tb, float *const *host_dev, TicketDev tk,
-                 int64_t n_miss, int32_t u, float *stage, const float *staged, hipStream_t s)
+                 int64_t n_miss, float *stage, const float *staged, hipStream_t s)
 {
     if (n_miss <= 0) return;
     const int D4 = dim / 4;
@@ -746,13 +746,12 @@ void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t
 }
 
 void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,
-                     const int32_t *slot_u, int64_t n_chunks, int64_t n_multi, int chunk,
+                     const int32_t *slot_u, int64_t n_chunks, int64_t n_multi,
                      const float *grad, int64_t nbags, float lr, float *partial, hipStream_t s,
                      hipEvent_t ev[4])
 {
     if (n_chunks <= 0) return;
     const int D4 = dim / 4;
-    (void)chunk;
     // one lane group of D4 / VPL lanes per chunk
     SP_DISPATCH_LPR_EV(D4, k_backward, grid_rows(n_chunks, D4 / bwd_vpl(D4)), ev[0], ev[1],
                        (float4 *)storage,

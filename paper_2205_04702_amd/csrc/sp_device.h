@@ -86,14 +86,6 @@ __device__ __forceinline__ T block_excl_scan_n(T v, T *lds, T &total)
     return base + incl - v;
 }
 
-template <typename T>
-__device__ __forceinline__ T block_sum(T v, T *lds)
-{
-    T total;
-    (void)block_excl_scan(v, lds, total);
-    return total;
-}
-
 // ---------------------------------------------------------------- segmented scan
 //
 // Segmented exclusive scan over index ranges in one launch (single pass with
@@ -108,11 +100,6 @@ __device__ __forceinline__ T block_sum(T v, T *lds)
 // 32-bit counter (uint32_t) or two independent 32-bit counters packed in a
 // uint64_t (low and high half, each sum below 2^32).
 
-struct SegDevN {  // one contiguous range [0, *n) whose length lives on the device
-    const int32_t *n;
-    __device__ int64_t beg(int) const { return 0; }
-    __device__ int64_t end(int) const { return *n; }
-};
 struct SegN {  // one contiguous range [0, n)
     int64_t n;
     __device__ int64_t beg(int) const { return 0; }

@@ -364,7 +364,7 @@ void launch_pf_arrange(const Tables &tb, PrefetchDev pf, int64_t n_own,
 // missing row m_key[i] into the slot: from `staged` row i when given (the
 // staged fill), else straight from the mapped host table.
 void launch_move(float *storage, int dim, const Tables &tb, float *const *host_dev, TicketDev tk,
-                 int64_t n_miss, int32_t u, float *stage, const float *staged, hipStream_t s);
+                 int64_t n_miss, float *stage, const float *staged, hipStream_t s);
 // Copies bytes (rounded up to whole 16-byte words; both ends 16-byte aligned)
 // from device memory to pinned host memory (its device-visible address).
 void launch_push(const void *src, void *dst, int64_t bytes, hipStream_t s);
@@ -378,7 +378,7 @@ void launch_forward(const float *storage, int dim, int64_t nslots, const int32_t
 constexpr int64_t STATIC_PARTIAL_BYTES = 32ll << 20;
 hipError_t static_partial_address(void **ptr);
 void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,
-                     const int32_t *slot_u, int64_t n_chunks, int64_t n_multi, int chunk,
+                     const int32_t *slot_u, int64_t n_chunks, int64_t n_multi,
                      const float *grad, int64_t nbags, float lr, float *partial, hipStream_t s,
                      hipEvent_t ev[4]);
 

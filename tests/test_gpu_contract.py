@@ -377,3 +377,20 @@ def test_window_length_changes(harness, hold_past):
     finally:
         ctx.close()
         host.close()
+
+
+def test_device_memory_per_id(harness):
+    """Device memory grows with max_ids by what is used: per ID and ring entry (5 of them at
+    lookahead 0) 28 bytes of batch arrays, 17 of chunks (16 per chunk, 1/16 of them spare),
+    4/17 of long runs and 28 of ticket arrays; once, 12 of victim lists, 4 + 4 of digit
+    counts, 16 of sort entries, 17 of partial sums (16 per chunk) and below 0.1 of scans."""
+    sizes = []
+    host = spm.HostTables([1000], 4)
+    for n in (1 << 20, 2 << 20):
+        ctx = spm.ScratchPipe([1000], 4, [10], 0, host, 16, n)
+        sizes.append(ctx.stats()["device_bytes"])
+        ctx.close()
+    host.close()
+    used = 5 * (28 + 17 + 4 / 17 + 28) + 12 + 8 + 16 + 17
+    slope = (sizes[1] - sizes[0]) / (1 << 20)
+    assert used - 0.5 < slope < used + 0.5, (slope, used)
