@@ -15,9 +15,11 @@
 // Ordering (the RAW dependences of Sec. IV-B, for one plan k in flight while
 // batch k-1 trains):
 //  1  update(k-1) -> forward(k): forward(k) waits for update(k-1)'s event.
-//  2/3 update or fill -> victim read: a victim last used by batch k-1 is packed
-//     and refilled only after update(k-1); other victims after update(k-2).
-//     The plan itself never evicts a slot any window batch uses.
+//  2/3 update or fill -> victim read: victims are packed and refilled after
+//     every update that may have used one: all up to update(k-1-P), as the rows
+//     of the past window's P batches are held (whichever batch used a victim
+//     last: the host does not read the victims).  The plan itself never evicts
+//     a slot any window batch uses.
 //  4  host write-back -> later fill of the same row: a row evicted by plan p is
 //     not in batches p..p+n_p-1 (the hold window), so before the fill of plan k
 //     the host joins every write-back job with p + n_p <= k.
@@ -1331,14 +1333,13 @@ static void copy_host(sp_ctx *h, void *dst, const void *src, int64_t bytes)
 // batch waits for this ingest, and that plan waits for the query.
 // `prestaged`: a batch from host memory already copied into the entry's
 // pinned buffers (by defer_ahead).
-static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead,
+static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead, hipStream_t si,
                         bool prestaged = false)
 {
     const int r = (int)(q % h->nring);
     BatchDev &b = h->ring[r];
     // this call returns only once the caller's device arrays have been read
     const bool caller_waits = bt.on_device && !ahead;
-    hipStream_t si = h->ingest_on_plan && ahead ? h->s_plan : h->s_ingest;
     if (h->ingest_last && si != h->ingest_last)
         HIPCHK(h, wait_unless_done(si, h->ring_ready[h->ingest_last_r]));
     // the previous occupant (batch q - nring) must be done with its backward
@@ -1445,7 +1446,7 @@ static sp_status issue_copy(sp_ctx *h, hipStream_t s)
 static sp_status ingest_ahead(sp_ctx *h, const sp_batch *window, int n, int nhold, int64_t k)
 {
     for (int w = nhold; w < n; ++w)
-        if (h->ring_batch[(k + w) % h->nring] != k + w) TRY(ingest(h, window[w], k + w, true));
+        if (h->ring_batch[(k + w) % h->nring] != k + w) TRY(ingest(h, window[w], k + w, true, h->ingest_on_plan ? h->s_plan : h->s_ingest));
     return SP_OK;
 }
 
@@ -1476,11 +1477,14 @@ static sp_status defer_ahead(sp_ctx *h, const sp_batch *window, int n, int from,
     return SP_OK;
 }
 
-// Enqueue the deferred ingests (behind the last update issued).
+// Enqueue the deferred ingests (behind the last update issued).  With prefetch
+// they stay on the ingest stream: the next plan arranges its missing keys on
+// the plan stream, and the gather would wait for that update.
 static sp_status ingest_deferred(sp_ctx *h)
 {
     const double t0 = host_ms();
-    for (const auto &d : h->deferred) TRY(ingest(h, d.bt, d.q, true, !d.bt.on_device));
+    hipStream_t si = h->ingest_on_plan && h->pf_depth == 0 ? h->s_plan : h->s_ingest;
+    for (const auto &d : h->deferred) TRY(ingest(h, d.bt, d.q, true, si, !d.bt.on_device));
     h->deferred.clear();
     h->host_ms[0] += host_ms() - t0;
     return SP_OK;
@@ -1800,7 +1804,7 @@ extern "C" sp_status sp_plan(sp_handle h, const sp_batch *window, int32_t n, int
         if (h->ring_batch[r] == q && (h->ring_nnz[r] != window[w].nnz || h->ring_B[r] != window[w].batch))
             return fail(h, SP_ERR_INVALID_ARG, "batch %lld changed shape between windows", (long long)q);
         if (w < nhold && h->ring_batch[r] != q) {
-            TRY(ingest(h, window[w], q, false));
+            TRY(ingest(h, window[w], q, false, h->s_ingest));
         }
     }
 

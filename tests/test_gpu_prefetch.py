@@ -214,3 +214,50 @@ def test_deeper_prefetch_overlapped_and_staged_equal_serialized(harness):
     for r in results[1:]:
         for x, y in zip(results[0], r):
             assert np.array_equal(x, y)
+
+
+def test_rows_are_gathered_while_the_update_before_runs(harness):
+    """Staged fill with write-backs above 8 MiB and deferred sorts: the missing keys of a plan
+    reach the host's gather without waiting for the update before, or for a sort behind it.
+    A row that changes in the host table while that update is still held up shows whether it
+    had been gathered by then."""
+    import time
+    import numpy as np
+    import torch
+    from paper_2205_04702_amd import scratchpipe as sp
+    n, dim, L, steps, k = 20_000, 128, 2, 9, 5  # rows a batch, all new; the update held up
+    assert n * dim * 4 > 8 << 20
+    _say("case gather beside a long update")
+    host = sp.host_tables([n * (steps + L + 3)], dim, "staged")
+    host[0][:] = np.arange(len(host[0]), dtype=np.float32)[:, None]
+    dev = torch.device("cuda:0")
+    off = torch.arange(n + 1, dtype=torch.int32, device=dev)
+    batches = [(off[:n] + n * s, off) for s in range(steps + L + 2)]
+    out = torch.zeros((n, dim), device=dev)
+    grad = torch.zeros((n, dim), device=dev)
+    busy = torch.zeros(1 << 28, device=dev)
+    torch.cuda.synchronize()
+    ctx = sp.ScratchPipe([len(host[0])], dim, [n * (L + 3)], L, host, n, n, prefetch=1,
+                         fill="staged", flags=sp.SP_FLAG_DEFER_SORTS)
+    try:
+        for s in range(steps):
+            t = ctx.plan(batches[s:s + L + 3])
+            if s == k + 1:  # it fills the rows of batch k + 2
+                time.sleep(0.05)
+                assert not held.query(), "the update was to be held up for longer"
+                host[0][n * (k + 2):n * (k + 3)] += 0.5
+            ctx.forward(t, out)
+            if s == k:  # some 0.2 s of passes over 1 GiB
+                for _ in range(400):
+                    busy.add_(1.0)
+            ctx.backward_update(t, grad, 0.0)
+            if s == k:
+                held = torch.cuda.Event()
+                held.record()
+            if s == k + 2:
+                want = torch.arange(n * s, n * (s + 1), device=dev).float()
+                assert bool((out == want[:, None]).all()), "gathered only after the update before"
+        assert ctx.stats()["evictions"] > 2 * n
+    finally:
+        ctx.close()
+        host.close()
