@@ -123,8 +123,8 @@ static int bag_parts(int64_t nnz, int64_t nbags)
 //  * k_sort_hist: digit counts of every tile and of every group of G tiles
 //    (one block per group);
 //  * k_sort_scatter: one block per tile.  It adds up its digit's group counts
-//    and the tile counts of its own group (no scan in between: G is near the
-//    square root of a table's tiles, so a thread adds some 2 * G counts), ranks its
+//    and the tile counts of its own group (no scan in between: a thread adds
+//    its table's groups and up to G tiles, sort_group), ranks its
 //    entries with wave ballots, puts them in digit order in LDS and writes
 //    each digit's entries as one run.
 // What bounds it: HBM traffic, 8 bytes read and written per entry and pass
@@ -1240,6 +1240,20 @@ SortWsSize sort_ws_size(int64_t n)
     return {2 * n, 2 * tiles * SORT_BINS, tiles};
 }
 
+// Tiles per group: a power of two up to the square root of a table's mean tiles,
+// so that a scatter block adds few group counts, but at least 256 groups in all,
+// one k_sort_hist block for each compute unit.  An ingest's time in us with 1024
+// and with 256 groups at least: one table of 4.2M IDs 425 and 350, of 21M 1780
+// and 1325 (a block adds 641 and 161 group counts); two of 10.5M 1450 and 1270;
+// four of 1M 331 and 280; 26 of 160k 205 and 196; 64 of 330k 750 and 750.  Groups
+// past the root cost: eight tables of 2.6M, 16 tiles each 1170 and 32 tiles 1205.
+static int sort_group(int64_t tiles, int T)
+{
+    int G = 1;
+    while ((int64_t)4 * G * G * T <= tiles && tiles / G > 256) G *= 2;
+    return G;
+}
+
 template <int NT, int ITEMS>
 static void launch_general(const Tables &tb, const BatchDev &b, const int32_t *ids,
                            const int32_t *bag_off, int32_t B, int64_t nnz, int64_t max_table_ids,
@@ -1256,8 +1270,7 @@ static void launch_general(const Tables &tb, const BatchDev &b, const int32_t *i
     }
     const int64_t flat = (nnz + TILE - 1) / TILE;
     const int64_t tiles = flat + tb.T;  // at least those of all tables, whatever their spans
-    int G = 1;  // near the square root of a table's tiles, with blocks for every compute unit
-    while (G < 32 && (int64_t)G * G * tb.T < flat && flat / G > 1024) G *= 2;
+    const int G = sort_group(flat, tb.T);
     const int64_t groups = flat / G + tb.T + 1;
     uint32_t *const thist = sw.hist, *const ghist = sw.hist + tiles * SORT_BINS;
     const int parts = bag_parts(nnz, nbags);

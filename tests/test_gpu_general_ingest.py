@@ -37,6 +37,20 @@ def test_general_ingest_edges(name, device_ids):
     gpu_harness.run_parity(w, max_table_ids=0, device_ids=device_ids, prepare_ahead=1)
 
 
+@pytest.mark.parametrize("ids", [300_000, 1_100_000, 2_200_000, 4_400_000])  # 2, 2, 4, 8 tiles
+def test_general_ingest_groups_of_tiles(ids):
+    """One long table between short ones, its tiles counted in groups, the last one partly filled."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from tests import gpu_harness
+    rows, bags = [300, ids // 3, 5000], 100
+    w = wl.custom(rows=rows, dim=4, batch=bags, pooling=[3, ids // bags, 41], slots=rows,
+                  lookahead=0, steps=2, dist=("zipf", 0.9), seed=9)
+    print(f"case groups of tiles, nnz {w.nnz}", flush=True)
+    gpu_harness.run_parity(w, max_table_ids=0)
+
+
 @pytest.mark.parametrize("longest", [1, 9, 200])
 def test_general_ingest_ragged(longest):
     """Bags of 0..longest IDs: empty ones at either end of a wave's 64, long ones across its steps."""
