@@ -328,9 +328,11 @@ __global__ void __launch_bounds__(BLOCK) k_query(int32_t row_bits, int32_t T, Hi
 }
 
 // IDs of the longest row from which a thread takes four keys, and eight.  Few
-// blocks contend less for the counters, many hide more of the chain: with one
-// key per thread 231k unique keys took 0.167 ms, 30k 13 us.
-constexpr int64_t QUERY_FOUR = 96 << 10, QUERY_EIGHT = 1 << 20;
+// blocks contend less for the counters, many hide more of the chain.  In us with
+// one, four and eight keys per thread, eight tables, all keys unique:
+//    48k  12.8 13.3 16.4     384k  46.0 19.6 19.2     1.5M  107 53.3 37.5
+//    96k  17.8 14.0 16.1     768k  67.9 30.6 24.4     3.1M  177 83.8 66.0
+constexpr int64_t QUERY_FOUR = 64 << 10, QUERY_EIGHT = 512 << 10;
 
 void launch_query(const Tables &tb, const HitMap &map,
                   const uint32_t *const *ukeys, const int32_t *const *nuniq, int nwin,
@@ -742,7 +744,10 @@ __global__ void __launch_bounds__(VS_THREADS) k_victim_sort(SelArgs a, const uin
 // thousand slots: 2048 slots 13.7 us (the launches it replaces, a level or more
 // of the select over all tables, the segmented scan and the sort, 8.4 + 9.8 +
 // 5.2 us and two more launches), 9000 slots 23 us (11.4 + 11.4 + 5.2), 100k
-// slots 146 us (25 + 17 + 7).
+// slots 146 us (25 + 17 + 7).  Around the line, in us from the first launch to the
+// last one's end, this and the launches it replaces: priorities of one digit (LRU
+// up to 2000 plans) 12k slots 26 29, 16k 29 to 42 and 27 to 31 (1, 8 and 26
+// tables), 24k 43 30; of three (random) 16k 55 59, 24k 81 93, 32k 98 107.
 constexpr int64_t SELECT_ONE_SLOTS = 16 << 10;
 constexpr uint32_t KEY_HELD = 0xFFFFFFFFu;  // priorities are below 2^31
 
@@ -1083,7 +1088,11 @@ __device__ __forceinline__ int32_t last_batch_with(const WindowKeys &wk, uint32_
 // hold_to of the entering keys) when large, by the chain of a fill when small.
 // 2.1M unique keys a batch: 1.03 ms while it also wrote a slot per position and
 // raised hold_to by atomics, 0.14 ms now.
-constexpr int64_t COMMIT_FOUR = 512 << 10;  // items from which a thread takes four
+// In us with one and four items per thread, at items (0.77M: 384k unique keys, all
+// cached, and as many entering): 0.77M 13.8 18.2, 1.5M 23.0 22.0, 6.1M 69 65, 12M 146
+// 118; 20M IDs of 64 tables, 2.1M unique, 160 104; with two misses in five keys 3.8M
+// 92 100.
+constexpr int64_t COMMIT_FOUR = 1 << 20;  // items from which a thread takes four
 template <int KPT, bool ONE>
 __global__ void __launch_bounds__(BLOCK) k_commit(HitMap map, TicketDev tk, int64_t n_miss,
                                                   int64_t n_unique, int64_t nslots,
