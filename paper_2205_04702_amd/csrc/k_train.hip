@@ -398,12 +398,23 @@ __global__ void __launch_bounds__(BLOCK) k_backward(float4 *__restrict__ storage
 // Runs longer than one chunk (listed in `multi`, any order): adds a run's chunk
 // partials in a fixed strided order (group g of the lane groups that work on
 // it takes chunks g, g + groups, ...; then the groups' sums in order) and
-// updates the row.  One wave takes a run; the few runs above COMBINE_WAVE
-// chunks (a hot row of a small table has thousands) are left to the whole
-// block, with eight partials in flight per lane, since the longest one ends
-// the launch.  With one block per run 21M IDs over 64 tables took 0.19 ms
-// alone, nearly all blocks adding a few partials with most lanes idle;
-// 0.135 ms now.
+// updates the row.  With few runs a block takes each (k_bwd_combine_few), so that
+// long ones, a hot row has thousands of chunks, are added side by side.  With many
+// most lanes of such blocks would add nothing: one wave takes a run, and the few
+// runs above COMBINE_WAVE chunks are left to the whole block, with eight partials
+// in flight per lane, one after another.  In us, few and many, rows of 16 / 64 /
+// 256 floats:
+//        8 runs of 3750 chunks   8 29 / 21 84 /  79 318
+//      520 runs of  512          7 15 / 12 22 /  55  96
+//     2.6k runs of  102          6 10 / 12 14 /  51  52
+//     4.8k runs of   26          6  4 /  8  7 /  20  21
+//     5.4k, Zipf                 9 11 / 14 16 /  36  45
+//      10k runs of   26         11  7 / 13 13 /  51  54
+//      14k, Zipf                20 16 / 27 27 /  95 125
+//      52k runs of    5         44 18 / 40 21 /  87  66
+// (COMBINE_WAVE at 256: 8 runs of 190 chunks of 256 floats 18 instead of 25 us, one
+// such run 16 instead of 8.)
+static bool few_runs(int64_t n_multi, int lpr) { return n_multi <= (lpr < 16 ? 4096 : 256 * lpr); }
 constexpr int COMBINE_WAVE = 64;
 
 template <int LPR, int UNROLL>
@@ -473,6 +484,31 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
         }
         __syncthreads();
     }
+}
+
+template <int LPR>
+__global__ void __launch_bounds__(BLOCK) k_bwd_combine_few(float4 *__restrict__ storage,
+                                                           const int32_t *__restrict__ multi,
+                                                           const int32_t *__restrict__ seg_chunk0,
+                                                           const int32_t *__restrict__ slot_u,
+                                                           const float4 *__restrict__ partial,
+                                                           int64_t nslots, float lr)
+{
+    constexpr int G = BLOCK / LPR;
+    __shared__ float4 red[G][LPR];
+    const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
+    const int32_t s = multi[blockIdx.x];
+    const int64_t c0 = seg_chunk0[s], nch = seg_chunk0[s + 1] - c0;
+    const int32_t slot = slot_u[s];
+    const bool ok = (uint32_t)slot < (uint64_t)nslots;
+    red[g][c] = sum_partials<LPR, 8>(partial + c0 * LPR + c, nch, g, G);
+    __syncthreads();
+    if (g != 0 || !ok) return;
+    float4 *const row = storage + (int64_t)slot * LPR + c;
+    const float4 x = nt_load(row);
+    float4 sum = red[0][c];
+    for (int q = 1; q < G; ++q) sum = f4_add(sum, red[q][c]);
+    nt_store(row, sgd_step(x, sum, lr));
 }
 
 // ---------------------------------------------------------------- evict / fill
@@ -757,11 +793,17 @@ void launch_backward(float *storage, int dim, int64_t nslots, const BatchDev &b,
                        (float4 *)storage,
                        (const int4 *)b.chunk_desc, (const int32_t *)b.sbag, slot_u, n_chunks,
                        (const float4 *)grad, nbags, nslots, lr, (float4 *)partial);
-    if (n_multi > 0)
+    if (n_multi <= 0) return;
+    if (few_runs(n_multi, D4))
+        SP_DISPATCH_LPR_EV(D4, k_bwd_combine_few, dim3((unsigned)n_multi), ev[2], ev[3],
+                           (float4 *)storage, (const int32_t *)b.multi,
+                           (const int32_t *)b.seg_chunk0, slot_u, (const float4 *)partial, nslots,
+                           lr)
+    else
         SP_DISPATCH_LPR_EV(D4, k_bwd_combine, grid_waves(n_multi), ev[2], ev[3],
                            (float4 *)storage, (const int32_t *)b.multi, n_multi,
                            (const int32_t *)b.seg_chunk0, slot_u,
-                           (const float4 *)partial, nslots, lr);
+                           (const float4 *)partial, nslots, lr)
 }
 
 }  // namespace sp
