@@ -397,8 +397,8 @@ __global__ void __launch_bounds__(BLOCK) k_backward(float4 *__restrict__ storage
 
 // Runs longer than one chunk (listed in `multi`, any order): adds a run's chunk
 // partials in a fixed strided order (group g of the lane groups that work on
-// it takes chunks g, g + groups, ...; then the groups' sums in order) and
-// updates the row.  With few runs a block takes each (k_bwd_combine_few), so that
+// it takes chunks g, g + groups, ...; then the groups' sums, in a fixed order
+// too) and updates the row.  With few runs a block takes each (k_bwd_combine_few), so that
 // long ones, a hot row has thousands of chunks, are added side by side.  With many
 // most lanes of such blocks would add nothing: one wave takes a run, and the few
 // runs above COMBINE_WAVE chunks are left to the whole block, with eight partials
@@ -494,21 +494,21 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine_few(float4 *__restrict__ 
                                                            const float4 *__restrict__ partial,
                                                            int64_t nslots, float lr)
 {
-    constexpr int G = BLOCK / LPR;
-    __shared__ float4 red[G][LPR];
+    constexpr int WAVES = BLOCK / WAVE, G = BLOCK / LPR;
+    static_assert(WAVES == 4, "the waves' sums are added in pairs");
+    __shared__ float4 red[WAVES][LPR];
     const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
     const int32_t s = multi[blockIdx.x];
     const int64_t c0 = seg_chunk0[s], nch = seg_chunk0[s + 1] - c0;
     const int32_t slot = slot_u[s];
     const bool ok = (uint32_t)slot < (uint64_t)nslots;
-    red[g][c] = sum_partials<LPR, 8>(partial + c0 * LPR + c, nch, g, G);
+    const float4 acc = reduce_rows<LPR>(sum_partials<LPR, 8>(partial + c0 * LPR + c, nch, g, G));
+    if (lane_id() < LPR) red[wave_id()][c] = acc;
     __syncthreads();
     if (g != 0 || !ok) return;
     float4 *const row = storage + (int64_t)slot * LPR + c;
-    const float4 x = nt_load(row);
-    float4 sum = red[0][c];
-    for (int q = 1; q < G; ++q) sum = f4_add(sum, red[q][c]);
-    nt_store(row, sgd_step(x, sum, lr));
+    const float4 sum = f4_add(f4_add(red[0][c], red[1][c]), f4_add(red[2][c], red[3][c]));
+    nt_store(row, sgd_step(nt_load(row), sum, lr));
 }
 
 // ---------------------------------------------------------------- evict / fill
