@@ -40,6 +40,20 @@ __device__ __forceinline__ float4 f4_add(float4 a, float4 b)
     return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
 }
 
+// Sum of N values (a power of two), in a tree.
+template <int N>
+__device__ __forceinline__ float4 f4_tree(const float4 (&v)[N])
+{
+    float4 t[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) t[k] = v[k];
+#pragma unroll
+    for (int o = N / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int k = 0; k < o; ++k) t[k] = f4_add(t[2 * k], t[2 * k + 1]);
+    return t[0];
+}
+
 __device__ __forceinline__ float4 f4_xor(float4 a, int o)
 {
     return make_float4(__shfl_xor(a.x, o, WAVE), __shfl_xor(a.y, o, WAVE), __shfl_xor(a.z, o, WAVE),
@@ -76,7 +90,7 @@ __device__ __forceinline__ float4 reduce_rows(float4 acc)
 // batch has single bags above FWD_LONG positions among shorter ones (SKEW) the
 // waves of a block share these, a whole wave for each.
 constexpr int FWD_ROWS = 8;
-constexpr int FWD_ACC = 4;
+constexpr int FWD_ACC = FWD_ROWS / 2;
 constexpr int fwd_lanes(int lpr) { return lpr < 8 ? 8 : lpr; }
 
 // The sum of the rows of one bag per group of GW lanes, in every lane of the
@@ -84,7 +98,9 @@ constexpr int fwd_lanes(int lpr) { return lpr < 8 ? 8 : lpr; }
 // as far as its longest (in 32 bits: fewer registers, more waves).  The group reads IB positions' slots at a time (the
 // next ones while this block's rows arrive) and broadcasts them by shuffles,
 // FWD_ROWS row loads in flight per lane.  Sums run over FWD_ACC partial sums
-// in position order.
+// in position order, two rows added to one another before each (rows one by
+// one on 4 partial sums are further from 64 bits than a wave per bag was: bags of 90
+// rows of 32 floats 9.7e-8, 8.0e-8 then).
 template <int LPR, int GW>
 __device__ __forceinline__ float4 bag_sum(const float4 *__restrict__ storage,
                                           const int32_t *__restrict__ inv,
@@ -142,7 +158,7 @@ __device__ __forceinline__ float4 bag_sum(const float4 *__restrict__ storage,
             }
             if (k0 == 0 && more) load_slots(base + IB);  // behind this batch's rows
 #pragma unroll
-            for (int q = 0; q < FWD_ROWS; ++q) acc[q % FWD_ACC] = f4_add(acc[q % FWD_ACC], v[q]);
+            for (int q = 0; q < FWD_ACC; ++q) acc[q] = f4_add(acc[q], f4_add(v[2 * q], v[2 * q + 1]));
         }
     }
 #pragma unroll
@@ -185,8 +201,7 @@ __device__ __forceinline__ float4 long_sum(const float4 *__restrict__ storage,
                 v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
                 if (k < n) v[q] = storage[(int64_t)r * LPR + c];
             }
-#pragma unroll
-            for (int q = 0; q < ROWS; ++q) acc = f4_add(acc, v[q]);
+            acc = f4_add(acc, f4_tree(v));
         }
     }
     return reduce_rows<LPR>(acc);
@@ -404,33 +419,36 @@ __global__ void __launch_bounds__(BLOCK) k_backward(float4 *__restrict__ storage
 // runs above COMBINE_WAVE chunks are left to the whole block, with eight partials
 // in flight per lane, one after another.  In us, few and many, rows of 16 / 64 /
 // 256 floats:
-//        8 runs of 3750 chunks   8 29 / 21 84 /  79 318
-//      520 runs of  512          7 15 / 12 22 /  55  96
+//        8 runs of 3750 chunks   7 29 / 20 84 /  75 318
+//      520 runs of  512          5 15 / 13 22 /  56  96
 //     2.6k runs of  102          6 10 / 12 14 /  51  52
 //     4.8k runs of   26          6  4 /  8  7 /  20  21
-//     5.4k, Zipf                 9 11 / 14 16 /  36  45
-//      10k runs of   26         11  7 / 13 13 /  51  54
-//      14k, Zipf                20 16 / 27 27 /  95 125
-//      52k runs of    5         44 18 / 40 21 /  87  66
+//     5.4k, Zipf                 9  8 / 14 13 /  35  45
+//      10k runs of   26         11  6 / 13 12 /  51  54
+//      14k, Zipf                20 13 / 27 23 /  85 125
+//      52k runs of    5         44 17 / 40 20 /  87  66
 // (COMBINE_WAVE at 256: 8 runs of 190 chunks of 256 floats 18 instead of 25 us, one
 // such run 16 instead of 8.)
 static bool few_runs(int64_t n_multi, int lpr) { return n_multi <= (lpr < 16 ? 4096 : 256 * lpr); }
 constexpr int COMBINE_WAVE = 64;
 
+// The partials p[q], q = g, g + groups, ..., UNROLL of them in flight and added in a
+// tree before the sum (one by one, the last ones each after the other, 26k runs of
+// 50 chunks of 256 floats were 5.2e-8 from 64 bits, with a block per run 4.2e-8).
 template <int LPR, int UNROLL>
 __device__ __forceinline__ float4 sum_partials(const float4 *__restrict__ p, int64_t nch,
                                                int64_t g, int64_t groups)
 {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    int64_t q = g;
-    for (; q + (UNROLL - 1) * groups < nch; q += UNROLL * groups) {
+    for (int64_t q = g; q < nch; q += UNROLL * groups) {
         float4 v[UNROLL];
 #pragma unroll
-        for (int k = 0; k < UNROLL; ++k) v[k] = p[(q + k * groups) * LPR];
-#pragma unroll
-        for (int k = 0; k < UNROLL; ++k) acc = f4_add(acc, v[k]);
+        for (int k = 0; k < UNROLL; ++k) {
+            v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (q + k * groups < nch) v[k] = p[(q + k * groups) * LPR];
+        }
+        acc = f4_add(acc, f4_tree(v));
     }
-    for (; q < nch; q += groups) acc = f4_add(acc, p[q * LPR]);
     return acc;
 }
 
@@ -445,6 +463,7 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
 {
     constexpr int WAVES = BLOCK / WAVE, G = BLOCK / LPR;
     __shared__ float4 red[G][LPR];
+    constexpr int WAVE_UNROLL = LPR == WAVE ? 8 : 4;  // one group: its own chain, as short by a tree of 8
     __shared__ int32_t left[WAVES];  // each wave's run, if the block is to add it
     const int w = wave_id(), lane = lane_id();
     const int64_t m = (int64_t)blockIdx.x * WAVES + w;
@@ -461,7 +480,7 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
         const bool ok = (uint32_t)slot < (uint64_t)nslots;
         float4 *const row = storage + (ok ? (int64_t)slot * LPR : 0) + c;
         const float4 x = nt_load(row);
-        float4 acc = sum_partials<LPR, 4>(partial + c0 * LPR + c, nch, lane / LPR, WAVE / LPR);
+        float4 acc = sum_partials<LPR, WAVE_UNROLL>(partial + c0 * LPR + c, nch, lane / LPR, WAVE / LPR);
         acc = reduce_rows<LPR>(acc);
         if (ok && lane < LPR) nt_store(row, sgd_step(x, acc, lr));
     }
