@@ -433,7 +433,7 @@ static bool few_runs(int64_t n_multi, int lpr) { return n_multi <= (lpr < 16 ? 4
 constexpr int COMBINE_WAVE = 64;
 
 // The partials p[q], q = g, g + groups, ..., UNROLL of them in flight and added in a
-// tree before the sum (one by one, the last ones each after the other, 26k runs of
+// tree before the sum (one by one, the last ones each after the other, 19k runs of
 // 50 chunks of 256 floats were 5.2e-8 from 64 bits, with a block per run 4.2e-8).
 template <int LPR, int UNROLL>
 __device__ __forceinline__ float4 sum_partials(const float4 *__restrict__ p, int64_t nch,
@@ -452,6 +452,25 @@ __device__ __forceinline__ float4 sum_partials(const float4 *__restrict__ p, int
     return acc;
 }
 
+// One run by the whole block: groups' sums by shuffles, then the waves' in pairs.
+template <int LPR>
+__device__ __forceinline__ void combine_by_block(float4 *__restrict__ storage,
+                                                 const float4 *__restrict__ partial, int64_t c0,
+                                                 int64_t nch, int32_t slot, int64_t nslots,
+                                                 float lr, float4 (&red)[BLOCK / WAVE][LPR])
+{
+    static_assert(BLOCK / WAVE == 4, "the waves' sums are added in pairs");
+    const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
+    const float4 acc = reduce_rows<LPR>(
+        sum_partials<LPR, 8>(partial + c0 * LPR + c, nch, g, BLOCK / LPR));
+    if (lane_id() < LPR) red[wave_id()][c] = acc;
+    __syncthreads();
+    if (g != 0 || (uint32_t)slot >= (uint64_t)nslots) return;
+    float4 *const row = storage + (int64_t)slot * LPR + c;
+    const float4 sum = f4_add(f4_add(red[0][c], red[1][c]), f4_add(red[2][c], red[3][c]));
+    nt_store(row, sgd_step(nt_load(row), sum, lr));
+}
+
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ storage,
                                                        const int32_t *__restrict__ multi,
@@ -461,9 +480,9 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
                                                        const float4 *__restrict__ partial,
                                                        int64_t nslots, float lr)
 {
-    constexpr int WAVES = BLOCK / WAVE, G = BLOCK / LPR;
-    __shared__ float4 red[G][LPR];
-    constexpr int WAVE_UNROLL = LPR == WAVE ? 8 : 4;  // one group: its own chain, as short by a tree of 8
+    constexpr int WAVES = BLOCK / WAVE;
+    constexpr int UNROLL = LPR == WAVE ? 8 : 4;  // a single group's chain is the longest
+    __shared__ float4 red[WAVES][LPR];
     __shared__ int32_t left[WAVES];  // each wave's run, if the block is to add it
     const int w = wave_id(), lane = lane_id();
     const int64_t m = (int64_t)blockIdx.x * WAVES + w;
@@ -480,27 +499,16 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine(float4 *__restrict__ stor
         const bool ok = (uint32_t)slot < (uint64_t)nslots;
         float4 *const row = storage + (ok ? (int64_t)slot * LPR : 0) + c;
         const float4 x = nt_load(row);
-        float4 acc = sum_partials<LPR, WAVE_UNROLL>(partial + c0 * LPR + c, nch, lane / LPR, WAVE / LPR);
-        acc = reduce_rows<LPR>(acc);
+        const float4 acc = reduce_rows<LPR>(sum_partials<LPR, UNROLL>(
+            partial + c0 * LPR + c, nch, lane / LPR, WAVE / LPR));
         if (ok && lane < LPR) nt_store(row, sgd_step(x, acc, lr));
     }
     __syncthreads();
     for (int k = 0; k < WAVES; ++k) {
         const int32_t run = left[k];
         if (run < 0) continue;  // uniform over the block
-        const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
         const int64_t b0 = seg_chunk0[run], n = seg_chunk0[run + 1] - b0;
-        red[g][c] = sum_partials<LPR, 8>(partial + b0 * LPR + c, n, g, G);
-        __syncthreads();
-        if (g == 0) {
-            float4 sum = red[0][c];
-            for (int q = 1; q < G; ++q) sum = f4_add(sum, red[q][c]);
-            const int32_t slot = slot_u[run];
-            if ((uint32_t)slot < (uint64_t)nslots) {
-                float4 *const row = storage + (int64_t)slot * LPR + c;
-                nt_store(row, sgd_step(nt_load(row), sum, lr));
-            }
-        }
+        combine_by_block<LPR>(storage, partial, b0, n, slot_u[run], nslots, lr, red);
         __syncthreads();
     }
 }
@@ -513,21 +521,10 @@ __global__ void __launch_bounds__(BLOCK) k_bwd_combine_few(float4 *__restrict__ 
                                                            const float4 *__restrict__ partial,
                                                            int64_t nslots, float lr)
 {
-    constexpr int WAVES = BLOCK / WAVE, G = BLOCK / LPR;
-    static_assert(WAVES == 4, "the waves' sums are added in pairs");
-    __shared__ float4 red[WAVES][LPR];
-    const int g = threadIdx.x / LPR, c = threadIdx.x % LPR;
+    __shared__ float4 red[BLOCK / WAVE][LPR];
     const int32_t s = multi[blockIdx.x];
     const int64_t c0 = seg_chunk0[s], nch = seg_chunk0[s + 1] - c0;
-    const int32_t slot = slot_u[s];
-    const bool ok = (uint32_t)slot < (uint64_t)nslots;
-    const float4 acc = reduce_rows<LPR>(sum_partials<LPR, 8>(partial + c0 * LPR + c, nch, g, G));
-    if (lane_id() < LPR) red[wave_id()][c] = acc;
-    __syncthreads();
-    if (g != 0 || !ok) return;
-    float4 *const row = storage + (int64_t)slot * LPR + c;
-    const float4 sum = f4_add(f4_add(red[0][c], red[1][c]), f4_add(red[2][c], red[3][c]));
-    nt_store(row, sgd_step(nt_load(row), sum, lr));
+    combine_by_block<LPR>(storage, partial, c0, nch, slot_u[s], nslots, lr, red);
 }
 
 // ---------------------------------------------------------------- evict / fill
