@@ -1332,7 +1332,7 @@ static void copy_host(sp_ctx *h, void *dst, const void *src, int64_t bytes)
 // after this sp_plan call returns: the query of the first plan that holds the
 // batch waits for this ingest, and that plan waits for the query.
 // `prestaged`: a batch from host memory already copied into the entry's
-// pinned buffers (by defer_ahead).
+// pinned buffers (by defer_ahead).  si: the stream that sorts it.
 static sp_status ingest(sp_ctx *h, const sp_batch &bt, int64_t q, bool ahead, hipStream_t si,
                         bool prestaged = false)
 {
@@ -1445,8 +1445,9 @@ static sp_status issue_copy(sp_ctx *h, hipStream_t s)
 // not in the ring yet.
 static sp_status ingest_ahead(sp_ctx *h, const sp_batch *window, int n, int nhold, int64_t k)
 {
+    hipStream_t si = h->ingest_on_plan ? h->s_plan : h->s_ingest;
     for (int w = nhold; w < n; ++w)
-        if (h->ring_batch[(k + w) % h->nring] != k + w) TRY(ingest(h, window[w], k + w, true, h->ingest_on_plan ? h->s_plan : h->s_ingest));
+        if (h->ring_batch[(k + w) % h->nring] != k + w) TRY(ingest(h, window[w], k + w, true, si));
     return SP_OK;
 }
 
